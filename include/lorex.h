@@ -472,8 +472,9 @@ lx_status lx_assign(const double* cost, int32_t n, int32_t* perm, double* total)
  * (output-side and input-side factors of W ~ W_dom + A B), sigma [r] fp64.
  * Solver: subspace iteration with the Gaussian test matrix omega
  * [cols][r + p] fp64 (device, caller-drawn), q power iterations, every
- * product orthonormalised (CholeskyQR2), then the eigendecomposition of the
- * small Gram matrix of Q^T R (cyclic Jacobi). All in fp64. A sketch
+ * product orthonormalised (Cholesky QR, the last one twice), then the
+ * eigendecomposition of the small Gram matrix of Q^T R (cyclic Jacobi). All in
+ * fp64. A sketch
  * direction the residual does not have (exactly low-rank R) yields a zero
  * basis column and carries no weight.
  *

@@ -11,88 +11,172 @@
 // left singular vectors and values of R L (M M^T = R G R^T), and B =
 // sigma^(-1/2) U_r^T R, so no Cholesky factor of G or its inverse is formed.
 //
-//   * k_dgemm: C = alpha op(A) op(B) (+ C when accumulate), fp64, 64 x 64
-//     output tiles, 16-deep K slabs through LDS, 4 x 4 outputs per thread;
-//     the workhorse of every product below (all are thin: one side is the
-//     sketch width l = r + p <= 128, or the cost matrix's f x f x 3d).
-//   * k_chol: one workgroup, G = R^T R for an l x l Gram matrix in LDS
-//     (right-looking, one column per step); k_trsm_rows: Y <- Y R^-1, one
-//     thread per row. Twice in a row they make CholeskyQR2, the
-//     orthonormalisation of the sketch.
-//   * k_jacobi: one workgroup, the eigendecomposition of the l x l matrix
-//     Q^T R R^T Q by cyclic Jacobi in the round-robin (tournament) order, so
-//     each step rotates l / 2 disjoint pairs at once; matrix in LDS,
-//     eigenvectors in global memory; then the eigenpairs sorted descending.
+//   * k_dgemm: C = op(A) op(B), fp64 on v_mfma_f64_16x16x4_f64, tiles chosen by
+//     the product's shape; the workhorse of every product below (all are
+//     thin: one side is the sketch width l = r + p <= 128, or the cost matrix's
+//     f x f x 3d).
+//   * k_chol: one workgroup, G = U^T U for an l x l Gram matrix held in
+//     registers (right-looking, one barrier per column); k_trsm_rows: Y <- Y
+//     U^-1, 16 lanes per row. Together they orthonormalise the sketch (once
+//     between the products, twice, CholeskyQR2, for the final basis).
+//   * k_jacobi: one workgroup, the eigenvalues of the l x l matrix Q^T R R^T Q
+//     by cyclic Jacobi in the round-robin (tournament) order, so each step
+//     rotates l / 2 disjoint pairs at once; matrix in LDS, rotations written
+//     to a log. k_jacobi_vec: the eigenvectors from the log, one wavefront per
+//     row of V, eigenpairs sorted descending.
 #include "lx_internal.h"
+
+#include <algorithm>
 
 namespace lx {
 namespace {
 
-constexpr int DG_T = 64, DG_K = 16;
+typedef double f64x4 __attribute__((ext_vector_type(4)));
 
-// Split-K: blockIdx.z takes K range [z kc, (z + 1) kc) and writes its
-// partial tile to C + z * M * N (ldc = N); k_dsum adds the partials in z
-// order.
-__global__ __launch_bounds__(256) void k_dgemm(int M, int N, int K, double alpha, const double* __restrict__ A,
-                                               int64_t lda, int ta, const double* __restrict__ B, int64_t ldb, int tb,
-                                               double* __restrict__ C, int64_t ldc, int kc) {
-  __shared__ double sA[DG_K][DG_T + 1];
-  __shared__ double sB[DG_K][DG_T + 1];
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  const int m0 = blockIdx.y * DG_T, n0 = blockIdx.x * DG_T;
+// Workgroup barrier for LDS communication only: waits for this wavefront's
+// LDS operations, not for its global stores (which nothing in the workgroup
+// reads back), unlike __syncthreads().
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0xF | (0x7 << 4) | (0x3 << 14));  // lgkmcnt(0)
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+// 1 / x to a unit in the last place for normal x: the hardware estimate and
+// two Newton steps (a dependent chain a third of a full division's).
+__device__ __forceinline__ double fast_rcp(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = fma(fma(-x, r, 1.0), r, r);
+  return fma(fma(-x, r, 1.0), r, r);
+}
+
+// 1 / sqrt(x), likewise.
+__device__ __forceinline__ double fast_rsq(double x) {
+  double r = __builtin_amdgcn_rsq(x);
+  r = fma(r * fma(-x * r, r, 1.0), 0.5, r);
+  return fma(r * fma(-x * r, r, 1.0), 0.5, r);
+}
+
+// C = op(A) op(B) in fp64 on the matrix cores: BM x BN output tiles, BM = 16 WM
+// MI and BN = 16 WN NI, by 4 wavefronts in a WM x WN grid of MI x NI
+// v_mfma_f64_16x16x4 blocks (lane l holds A row / B column l % 16 at k = l /
+// 16; accumulator i is row 4 i + l / 16, column l % 16). 32-deep K slabs, double-
+// buffered in LDS as [row][k] with a pitch of 34 doubles: the 32 lanes of
+// half a ds_read_b64 (16 rows, 2 k) then fall on 64 distinct banks. The next
+// slab's global loads are in flight during the MFMAs, and one barrier
+// separates slabs. Bound by the loads' latency at the sizes it runs at (a few
+// K slabs per workgroup), so split-K spreads a product over the chip.
+// Against the VALU kernel it replaced (64 x 64 tiles, 4 x 4 outputs per thread):
+// the cost product 768 x 768 x 6144 1237 -> 200 us, the sketch product 768 x
+// 74 x 2048 55 -> 16 us.
+//
+// Split-K: blockIdx.z takes K range [z kc, (z + 1) kc) and writes its partial
+// tile to C + z * M * N (ldc = N); the consumer adds the partials in z order.
+// TI: element type of A and B (double, or float for the alignment cost's
+// neuron vectors, which fp32 holds exactly).
+constexpr int DG_K = 32, DG_PITCH = 34;
+
+template <typename TI, int WM, int WN, int MI, int NI>
+__global__ __launch_bounds__(256) void k_dgemm(int M, int N, int K, const TI* __restrict__ A, int64_t lda, int ta,
+                                               const TI* __restrict__ B, int64_t ldb, int tb, double* __restrict__ C,
+                                               int64_t ldc, int kc) {
+  static_assert(WM * WN == 4, "4 wavefronts");
+  constexpr int BM = 16 * WM * MI, BN = 16 * WN * NI;
+  constexpr int RA = BM * DG_K / 256, RB = BN * DG_K / 256;  // elements per thread and slab
+  extern __shared__ double s_dg[];  // A slabs [2][BM][DG_PITCH], B slabs [2][BN][DG_PITCH]
+  double* const sA = s_dg;
+  double* const sB = s_dg + 2 * BM * DG_PITCH;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int wm = wave / WN, wn = wave % WN;
+  const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
   const int kbeg = blockIdx.z * kc, kend = kbeg + kc < K ? kbeg + kc : K;
   C += (int64_t)blockIdx.z * M * N;
-  double acc[4][4] = {};
+
+  // Element q of a thread's share of a slab of X (rows x K): with k contiguous
+  // in memory 32 consecutive threads take one row's 32 values, with the rows
+  // contiguous consecutive threads take consecutive rows. Rows past the edge
+  // are clamped (their products are never stored), k past the end gives 0.
+  auto load = [&](const TI* __restrict__ X, int64_t ld, bool kcontig, int r0, int rows, int rn, int k0, int q) -> TI {
+    const int e = q * 256 + tid;
+    const int r = kcontig ? e / DG_K : e % rn, k = kcontig ? e % DG_K : e / rn;
+    const int gr = r0 + r < rows ? r0 + r : rows - 1, gk = k0 + k < kend ? k0 + k : kend - 1;
+    const TI v = kcontig ? X[(int64_t)gr * ld + gk] : X[(int64_t)gk * ld + gr];
+    return k0 + k < kend ? v : (TI)0;
+  };
+  auto slot = [&](bool kcontig, int rn, int q) {
+    const int e = q * 256 + tid;
+    const int r = kcontig ? e / DG_K : e % rn, k = kcontig ? e % DG_K : e / rn;
+    return r * DG_PITCH + k;
+  };
+  const bool ka = !ta, kb = tb != 0;  // k contiguous in A, in B
+  TI va[RA], vb[RB];
+  auto fetch = [&](int k0) {
+#pragma unroll
+    for (int q = 0; q < RA; ++q) va[q] = load(A, lda, ka, m0, M, BM, k0, q);
+#pragma unroll
+    for (int q = 0; q < RB; ++q) vb[q] = load(B, ldb, kb, n0, N, BN, k0, q);
+  };
+  auto put = [&](int st) {
+#pragma unroll
+    for (int q = 0; q < RA; ++q) sA[st * BM * DG_PITCH + slot(ka, BM, q)] = (double)va[q];
+#pragma unroll
+    for (int q = 0; q < RB; ++q) sB[st * BN * DG_PITCH + slot(kb, BN, q)] = (double)vb[q];
+  };
+
+  f64x4 acc[MI][NI] = {};
+  if (kbeg < kend) {
+    fetch(kbeg);
+    put(0);
+  }
+  int st = 0;
   for (int k0 = kbeg; k0 < kend; k0 += DG_K) {
-    for (int q = threadIdx.x; q < DG_K * DG_T; q += 256) {
-      const int kk = q / DG_T, mm = q % DG_T;
-      const int gm = m0 + mm, gk = k0 + kk;
-      double va = 0.0;
-      if (gm < M && gk < kend) va = ta ? A[(int64_t)gk * lda + gm] : A[(int64_t)gm * lda + gk];
-      sA[kk][mm] = va;
-      const int gn = n0 + mm;
-      double vb = 0.0;
-      if (gn < N && gk < kend) vb = tb ? B[(int64_t)gn * ldb + gk] : B[(int64_t)gk * ldb + gn];
-      sB[kk][mm] = vb;
+    const bool more = k0 + DG_K < kend;
+    lds_barrier();
+    if (more) fetch(k0 + DG_K);
+    const double* const pa = &sA[st * BM * DG_PITCH + (wm * 16 * MI + (lane & 15)) * DG_PITCH + (lane >> 4)];
+    const double* const pb = &sB[st * BN * DG_PITCH + (wn * 16 * NI + (lane & 15)) * DG_PITCH + (lane >> 4)];
+#pragma unroll
+    for (int kk = 0; kk < DG_K; kk += 4) {
+      double fa[MI], fb[NI];
+#pragma unroll
+      for (int i = 0; i < MI; ++i) fa[i] = pa[i * 16 * DG_PITCH + kk];
+#pragma unroll
+      for (int j = 0; j < NI; ++j) fb[j] = pb[j * 16 * DG_PITCH + kk];
+#pragma unroll
+      for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[i], fb[j], acc[i][j], 0, 0, 0);
     }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < DG_K; ++kk) {
-      double a[4], b[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = sA[kk][ty * 4 + i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = sB[kk][tx * 4 + j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fma(a[i], b[j], acc[i][j]);
-    }
-    __syncthreads();
+    // (the other stage's readers passed this slab's barrier)
+    if (more) put(st ^ 1);
+    st ^= 1;
   }
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < MI; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int gm = m0 + ty * 4 + i, gn = n0 + tx * 4 + j;
-      if (gm < M && gn < N) C[(int64_t)gm * ldc + gn] = alpha * acc[i][j];
-    }
+    for (int j = 0; j < NI; ++j)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int gm = m0 + (wm * MI + i) * 16 + 4 * u + (lane >> 4), gn = n0 + (wn * NI + j) * 16 + (lane & 15);
+        if (gm < M && gn < N) C[(int64_t)gm * ldc + gn] = acc[i][j][u];
+      }
 }
 
-__global__ __launch_bounds__(256) void k_dsum(const double* __restrict__ part, int S, int M, int N,
-                                              double* __restrict__ C, int64_t ldc) {
+__global__ __launch_bounds__(256) void k_dsum(const double* __restrict__ part, int S, int64_t n,
+                                              double* __restrict__ C) {
   const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= (int64_t)M * N) return;
+  if (q >= n) return;
   double v = part[q];
-  for (int z = 1; z < S; ++z) v += part[(int64_t)z * M * N + q];
-  C[(q / N) * ldc + q % N] = v;
+  for (int z = 1; z < S; ++z) v += part[z * n + q];
+  C[q] = v;
 }
 
-// Neuron vectors of an expert, fp64 [f][3d]: row i = (gate[i, :], up[i, :],
-// down[:, i]); bf16 or fp32 storage.
+// Neuron vectors of an expert, fp32 [f][3d] (exact for bf16 and fp32 weights):
+// row i = (gate[i, :], up[i, :], down[:, i]); squared norms in fp64.
 __global__ __launch_bounds__(256) void k_neurons(const void* __restrict__ gate, const void* __restrict__ up,
                                                  const void* __restrict__ down, int bf16, int f, int d,
-                                                 double* __restrict__ out, double* __restrict__ norms) {
+                                                 float* __restrict__ out, double* __restrict__ norms) {
   const int i = blockIdx.x;
   __shared__ double s_red[256];
   double s = 0.0;
@@ -109,10 +193,9 @@ __global__ __launch_bounds__(256) void k_neurons(const void* __restrict__ gate, 
       base = down;
       src = (int64_t)(c - 2 * d) * f + i;
     }
-    const double v = bf16 ? (double)__uint_as_float((uint32_t)((const uint16_t*)base)[src] << 16)
-                          : (double)((const float*)base)[src];
+    const float v = bf16 ? __uint_as_float((uint32_t)((const uint16_t*)base)[src] << 16) : ((const float*)base)[src];
     out[(int64_t)i * 3 * d + c] = v;
-    s += v * v;
+    s += (double)v * (double)v;
   }
   s_red[threadIdx.x] = s;
   __syncthreads();
@@ -123,12 +206,16 @@ __global__ __launch_bounds__(256) void k_neurons(const void* __restrict__ gate, 
   if (threadIdx.x == 0) norms[i] = s_red[0];
 }
 
-// C[i][j] = na[i] + nb[j] - 2 G[i][j], in place over G.
+// C[i][j] = na[i] + nb[j] - 2 G[i][j], G the sum of the S partial products in
+// part (S = 1: part may be C itself).
 __global__ __launch_bounds__(256) void k_cost_finish(const double* __restrict__ na, const double* __restrict__ nb,
-                                                     int f, double* __restrict__ G) {
+                                                     int f, const double* part, int S, double* C) {
   const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= (int64_t)f * f) return;
-  G[q] = na[q / f] + nb[q % f] - 2.0 * G[q];
+  const int64_t ff = (int64_t)f * f;
+  if (q >= ff) return;
+  double g = part[q];
+  for (int z = 1; z < S; ++z) g += part[z * ff + q];
+  C[q] = na[q / f] + nb[q % f] - 2.0 * g;
 }
 
 // R[i][j] = W_m^P[i][j] - W_dom[i][j]: member rows (axis 0) or columns
@@ -155,195 +242,392 @@ __global__ __launch_bounds__(256) void k_residual(const void* __restrict__ wd, c
   R[q] = vm - vd;
 }
 
-// Cholesky of the l x l Gram matrix G (row-major), upper factor U with
-// G = U^T U written to Rf (zero below the diagonal).
-// A pivot at or below 1e-14 of the largest diagonal entry of G (a direction
-// the sketch does not have: exactly low-rank residuals) gives a zero row of
-// U, and k_trsm_rows then a zero column of Q; the directions kept stay
+// Cholesky of the l x l Gram matrix G = the sum of S partial products (row-
+// major), upper factor U with G = U^T U written to Uf (zero below the
+// diagonal). A pivot at or below 1e-14 of the largest diagonal entry of G (a
+// direction the sketch does not have: exactly low-rank residuals) gives a zero
+// row of U, and k_trsm_rows then a zero column of Q; the directions kept stay
 // orthonormal and the zero ones carry no weight in Q^T R.
-__global__ __launch_bounds__(1024) void k_chol(const double* __restrict__ G, int l, double* __restrict__ Rf) {
-  extern __shared__ double s_g[];  // [l][l]
-  __shared__ double s_gmax;
-  const int tid = threadIdx.x, nth = blockDim.x;
-  for (int q = tid; q < l * l; q += nth) s_g[q] = G[q];
-  __syncthreads();
-  if (tid == 0) {
-    double g = 0.0;
-    for (int k = 0; k < l; ++k) g = fmax(g, s_g[k * l + k]);
-    s_gmax = g;
+// Latency-bound (one workgroup, l dependent columns): thread (ti, tj) of a 16 x
+// 16 grid keeps entries (ti + 16 a, tj + 16 b) in registers, row k of the trailing
+// matrix goes through LDS once (one barrier per column), and the division by
+// the pivot's square root waits until every row is known. Against the kernel
+// that kept the matrix in LDS (1024 threads, three barriers per column): l = 74
+// 61 -> 32 us, the sum of the partials included.
+template <int NB>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_chol(const double* __restrict__ part, int S, int l, double* __restrict__ Uf) {
+  extern __shared__ double s_row[];  // [l][16 NB]: the trailing matrix's row k when its column is eliminated
+  __shared__ double s_diag[16 * NB];
+  constexpr int P = 16 * NB;
+  const int tid = threadIdx.x, ti = tid >> 4, tj = tid & 15;
+  double a[NB][NB] = {};
+  // every partial's entries are loaded together (clamped past l, then dropped)
+  for (int z = 0; z < S; ++z) {
+    const double* const g = part + (int64_t)z * l * l;
+    double t[NB][NB];
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+      for (int j = 0; j < NB; ++j) {
+        const int gi = ti + 16 * i, gj = tj + 16 * j;
+        t[i][j] = g[(gi < l ? gi : l - 1) * l + (gj < l ? gj : l - 1)];
+      }
+    __builtin_amdgcn_sched_barrier(0);  // all loads issued before the first is waited for
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+      for (int j = 0; j < NB; ++j) a[i][j] += t[i][j];
   }
-  __syncthreads();
-  const double floor_ = 1e-14 * s_gmax;
-  for (int k = 0; k < l; ++k) {
-    // row k of U: U[k][k] = sqrt(G[k][k]), U[k][j] = G[k][j] / U[k][k]
-    __syncthreads();
-    const double pk = s_g[k * l + k];
-    const double dkk = pk > floor_ ? sqrt(pk) : 0.0;
-    __syncthreads();
-    for (int j = k + tid; j < l; j += nth) s_g[k * l + j] = j == k ? dkk : (dkk > 0.0 ? s_g[k * l + j] / dkk : 0.0);
-    __syncthreads();
-    // trailing update: G[i][j] -= U[k][i] U[k][j] for i, j > k
-    const int m = l - k - 1;
-    for (int q = tid; q < m * m; q += nth) {
-      const int i = k + 1 + q / m, j = k + 1 + q % m;
-      s_g[i * l + j] -= s_g[k * l + i] * s_g[k * l + j];
+#pragma unroll
+  for (int i = 0; i < NB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      const int gi = ti + 16 * i, gj = tj + 16 * j;
+      if (gi >= l || gj >= l) a[i][j] = 0.0;
+      if (gi == gj) s_diag[gi] = a[i][j];
     }
+  lds_barrier();
+  double gmax = 0.0;
+  for (int k = 0; k < l; ++k) gmax = fmax(gmax, s_diag[k]);
+  const double floor_ = 1e-14 * gmax;
+#pragma unroll
+  for (int kb = 0; kb < NB; ++kb)
+    for (int kr = 0; kr < 16; ++kr) {
+      const int k = kb * 16 + kr;
+      if (k >= l) break;
+      double* const row = s_row + k * P;
+      if (ti == kr) {
+#pragma unroll
+        for (int j = 0; j < NB; ++j) row[tj + 16 * j] = a[kb][j];
+      }
+      lds_barrier();
+      const double pk = row[k];
+      const double inv = pk > floor_ ? fast_rcp(pk) : 0.0;
+      // rows and columns of the blocks before kb are done
+      double rj[NB];
+#pragma unroll
+      for (int j = kb; j < NB; ++j) rj[j] = row[tj + 16 * j];
+#pragma unroll
+      for (int i = kb; i < NB; ++i) {
+        const double ri = -row[ti + 16 * i] * inv;
+#pragma unroll
+        for (int j = kb; j < NB; ++j) a[i][j] = fma(ri, rj[j], a[i][j]);
+      }
+    }
+  lds_barrier();
+#pragma unroll 4
+  for (int q = tid; q < l * l; q += 256) {
+    const int k = q / l, j = q % l;
+    const double pk = s_row[k * P + k];
+    Uf[q] = j < k || !(pk > floor_) ? 0.0 : j == k ? sqrt(pk) : s_row[k * P + j] / sqrt(pk);
   }
-  __syncthreads();
-  for (int q = tid; q < l * l; q += nth) Rf[q] = (q % l) >= (q / l) ? s_g[q] : 0.0;
+}
+
+// Value of lane N of each row of 16 lanes, in every lane of the row.
+template <int N>
+__device__ __forceinline__ double row_bcast(double x) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, x);
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, 0x150 + N, 0xf, 0xf, false);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), 0x150 + N, 0xf, 0xf, false);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
 
 // Y[i, :] <- Y[i, :] U^-1 for the upper-triangular l x l U: x U = y, solved
-// left to right, one thread per row; U and the workgroup's rw rows (pitch
-// l + 1) staged in LDS.
-__global__ __launch_bounds__(64) void k_trsm_rows(double* __restrict__ Y, int rows, int l, int rw,
-                                                  const double* __restrict__ U) {
-  extern __shared__ double s_t[];
-  double* const su = s_t;
-  double* const sy = s_t + l * l;
-  const int r0 = blockIdx.x * rw, tid = threadIdx.x;
-  const int nr = rows - r0 < rw ? rows - r0 : rw;
-  for (int q = tid; q < l * l; q += 64) su[q] = U[q];
-  for (int q = tid; q < nr * l; q += 64) sy[(q / l) * (l + 1) + q % l] = Y[(int64_t)(r0 + q / l) * l + q % l];
-  __syncthreads();
-  if (tid < nr) {
-    double* const y = sy + tid * (l + 1);
-    for (int j = 0; j < l; ++j) {
-      double acc = y[j];
-      for (int k = 0; k < j; ++k) acc -= y[k] * su[k * l + j];
-      const double ujj = su[j * l + j];
-      y[j] = ujj != 0.0 ? acc / ujj : 0.0;
-    }
-  }
-  __syncthreads();
-  for (int q = tid; q < nr * l; q += 64) Y[(int64_t)(r0 + q / l) * l + q % l] = sy[(q / l) * (l + 1) + q % l];
+// left to right. 16 lanes hold one row (column c + 16 b in register b of lane
+// c), so a wavefront solves 4 rows: column j's value is finished in its lane,
+// broadcast over the row (DPP) and taken off the later columns. U is staged in
+// LDS (pitch 16 NB, zero past l) with its diagonal and reciprocals beside it.
+// Latency-bound: the chain is one division, one broadcast and one FMA per
+// column. Against one thread per row (12 workgroups for 768 rows): l = 74, 768
+// rows 100 -> 9 us.
+constexpr int kTrsmRows = 16;  // rows per workgroup of 4 wavefronts
+
+template <int NB, int J>
+__device__ __forceinline__ void trsm_step(double (&y)[NB], const double* su, const double* sd, const double* sr, int c) {
+  constexpr int P = 16 * NB, B = J / 16;
+  const double u = sd[J], r = sr[J];
+  double q = y[B] * r;
+  q = fma(fma(-q, u, y[B]), r, q);  // y / u, correctly rounded but for ties
+  const double v = row_bcast<J % 16>(q);
+  if (c == J % 16) y[B] = q;
+  const double* const row = su + J * P + c;
+  // columns of register B after J (U is 0 at and before J: the diagonal is
+  // kept apart)
+  y[B] = fma(-v, row[16 * B], y[B]);
+#pragma unroll
+  for (int b = B + 1; b < NB; ++b) y[b] = fma(-v, row[16 * b], y[b]);
 }
 
-inline int trsm_rows_per_wg(int l) { return l <= 96 ? 64 : 16; }
-inline size_t trsm_lds(int l) { return ((size_t)l * l + (size_t)trsm_rows_per_wg(l) * (l + 1)) * sizeof(double); }
+template <int NB, int J>
+__device__ __forceinline__ void trsm_all(double (&y)[NB], const double* su, const double* sd, const double* sr, int c) {
+  if constexpr (J < 16 * NB) {
+    trsm_step<NB, J>(y, su, sd, sr, c);
+    trsm_all<NB, J + 1>(y, su, sd, sr, c);
+  }
+}
 
-// Eigendecomposition of the symmetric l x l M (l even after padding with a
-// zero row/column when odd): cyclic Jacobi, round-robin pair order; V
-// (lp x lp row-major, in LDS when both fit, else global) accumulates the
-// rotations. Output: eigenvalues
-// descending in w[0..l), eigenvectors as columns of Vs (sorted).
-template <bool VLDS>
-__global__ __launch_bounds__(1024) void k_jacobi(const double* __restrict__ Min, int l, int lp,
-                                                 double* __restrict__ Vg, double* __restrict__ w,
-                                                 double* __restrict__ Vs, int max_sweeps) {
-  extern __shared__ double s_m[];  // [lp][lp], then V [lp][lp] when VLDS
-  double* const V = VLDS ? s_m + lp * lp : Vg;
-  __shared__ int s_p[64], s_q[64];
-  __shared__ double s_c[64], s_s[64];
-  __shared__ int s_order[128];
-  __shared__ double s_red[1024];
-  const int tid = threadIdx.x, nth = blockDim.x;
+template <int NB>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 2))) void k_trsm_rows(double* __restrict__ Y, int rows, int l, const double* __restrict__ U) {
+  extern __shared__ double su[];  // [16 NB][16 NB], strictly upper part
+  constexpr int P = 16 * NB;
+  __shared__ double sd[P], sr[P];
+  const int tid = threadIdx.x, c = tid & 15;
+  const int r = blockIdx.x * kTrsmRows + (tid >> 4);
+  double y[NB];
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    const int j = c + 16 * b;
+    y[b] = r < rows && j < l ? Y[(int64_t)r * l + j] : 0.0;
+  }
+  double uv[NB * NB];
+#pragma unroll
+  for (int u = 0; u < NB * NB; ++u) {
+    const int q = tid + u * 256, k = q / P, j = q % P;
+    uv[u] = U[(k < l ? k : l - 1) * l + (j < l ? j : l - 1)];
+  }
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int u = 0; u < NB * NB; ++u) {
+    const int q = tid + u * 256, k = q / P, j = q % P;
+    const double v = k < l && j < l ? uv[u] : 0.0;
+    su[q] = j > k ? v : 0.0;
+    if (j == k) {
+      sd[k] = v;
+      sr[k] = v != 0.0 ? 1.0 / v : 0.0;
+    }
+  }
+  lds_barrier();
+  trsm_all<NB, 0>(y, su, sd, sr, c);
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    const int j = c + 16 * b;
+    if (r < rows && j < l) Y[(int64_t)r * l + j] = y[b];
+  }
+}
+
+// Round-robin pairing of lp elements: element 0 is fixed, the others rotate;
+// pair x of step `step` joins slots x and lp - 1 - x.
+__device__ __forceinline__ int rr_pos(int x, int step, int lp) {
+  const int y = x - 1 + step;
+  return x == 0 ? 0 : 1 + (y >= lp - 1 ? y - (lp - 1) : y);
+}
+
+// The rotation of a pair: t = sgn(tau) / (|tau| + sqrt(1 + tau^2)) for tau =
+// (aqq - app) / (2 apq), by half angles: two reciprocal square roots in the
+// dependent chain, no division.
+__device__ __forceinline__ void jacobi_rot(double app, double aqq, double apq, double& c, double& s, double& t) {
+  c = 1.0;
+  s = t = 0.0;
+  if (apq == 0.0) return;
+  const double d = aqq - app, b = 2.0 * fabs(apq), ad = fabs(d);
+  // (tau = 0 counts as positive)
+  const bool pos = d == 0.0 || (d > 0.0) == (apq > 0.0);
+  const double sum = ad + b;
+  if (sum > 1e-140 && sum < 1e140) {
+    // half angles: cos 2a = |d| / h, h = sqrt(d^2 + b^2); c^2 = (1 + cos 2a) / 2,
+    // s = b / (2 h c)
+    const double y = fast_rsq(fma(d, d, b * b));
+    const double c2 = fma(0.5 * ad, y, 0.5);
+    const double rc = fast_rsq(c2);
+    c = c2 * rc;
+    s = 0.5 * b * y * rc;
+    t = s * rc;
+  } else {  // d^2 or b^2 could leave the range
+    const double tau = ad / b;
+    t = 1.0 / (tau + sqrt(1.0 + tau * tau));
+    c = 1.0 / sqrt(1.0 + t * t);
+    s = t * c;
+  }
+  if (!pos) {
+    s = -s;
+    t = -t;
+  }
+}
+
+// Eigenvalues of the symmetric l x l M (padded with a zero row and column
+// when l is odd): cyclic Jacobi, round-robin pair order. Per step wavefront 0
+// computes the rotations and their pairs' own entries, while the other threads
+// read their 2 x 2 blocks (pair k1's rows, pair k2's columns, k1 < k2; only
+// entries (i, j) with i <= j are kept); after a barrier they apply both sides
+// of the rotation at once. The rotations go to
+// log[(sweep * (lp - 1) + step) * lp / 2 + pair] for k_jacobi_vec; meta: the
+// number of sweeps, then the eigenvalue order. Latency-bound (one workgroup,
+// (lp - 1) steps per sweep). Against the kernel that rotated rows, columns and
+// V in LDS in two passes: l = 74 1328 -> 480 us with the vectors' kernel.
+__global__ __launch_bounds__(1024) void k_jacobi(const double* __restrict__ Min, int l, int lp, double* __restrict__ w,
+                                                 double2* __restrict__ log, int32_t* __restrict__ meta,
+                                                 int max_sweeps) {
+  extern __shared__ double s_m[];  // [lp][lp + 1], upper triangle (an odd pitch: rows and columns on distinct banks)
+  __shared__ double2 s_cs[64];
+  __shared__ double s_red[16];
+  const int pt = lp + 1;
+  const int tid = threadIdx.x, nth = blockDim.x, lane = tid & 63, wave = tid >> 6;
   for (int q = tid; q < lp * lp; q += nth) {
     const int i = q / lp, j = q % lp;
-    s_m[q] = (i < l && j < l) ? Min[i * l + j] : 0.0;
-    V[q] = i == j ? 1.0 : 0.0;
+    s_m[i * pt + j] = (i < l && j < l) ? Min[i * l + j] : 0.0;
   }
-  __syncthreads();
+  lds_barrier();
   // sum of squares of all entries (diag = 1) or of the off-diagonal ones
   auto sumsq = [&](bool diag) {
     double t = 0.0;
-    for (int q = tid; q < lp * lp; q += nth)
-      if (diag || q / lp != q % lp) t += s_m[q] * s_m[q];
-    s_red[tid] = t;
-    __syncthreads();
-    for (int o = nth / 2; o > 0; o >>= 1) {
-      if (tid < o) s_red[tid] += s_red[tid + o];
-      __syncthreads();
+    for (int q = tid; q < lp * lp; q += nth) {
+      const int i = q / lp, j = q % lp;
+      const double v = s_m[i * pt + j];
+      if (i < j) t += 2.0 * v * v;
+      if (diag && i == j) t += v * v;
     }
-    const double r = s_red[0];
-    __syncthreads();
+    for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o, 64);
+    if (lane == 0) s_red[wave] = t;
+    lds_barrier();
+    double r = 0.0;
+    for (int i = 0; i < (nth >> 6); ++i) r += s_red[i];
+    lds_barrier();
     return r;
   };
   const double norm0 = sumsq(true);
-  const int half = lp / 2;
-  for (int sweep = 0; sweep < max_sweeps; ++sweep) {
+  const int half = lp / 2, nblk = half * (half - 1) / 2;
+  // this thread's blocks (wavefronts 1 ..): pairs k1 < k2, at most 64 * 63 / 2 =
+  // 2016 blocks in 3 rounds of 960 threads
+  const int bth = nth - 64;
+  int kk[3];
+#pragma unroll
+  for (int u = 0; u < 3; ++u) {
+    int x = tid - 64 + u * bth;
+    kk[u] = -1;
+    if (tid >= 64 && x < nblk) {
+      int k1 = 0;
+      while (x >= half - 1 - k1) {
+        x -= half - 1 - k1;
+        ++k1;
+      }
+      kk[u] = k1 | ((k1 + 1 + x) << 16);
+    }
+  }
+  int sweep = 0;
+  for (; sweep < max_sweeps; ++sweep) {
     if (!(sumsq(false) > 1e-30 * norm0)) break;
     for (int step = 0; step < lp - 1; ++step) {
-      // round-robin pairing: element 0 fixed, the others rotate
+      int at[3][4];
+      double m[3][4];
       if (tid < half) {
-        auto pos = [&](int x) { return x == 0 ? 0 : 1 + (x - 1 + step) % (lp - 1); };
-        int a = pos(tid), b = pos(lp - 1 - tid);
+        const int a = rr_pos(tid, step, lp), b = rr_pos(lp - 1 - tid, step, lp);
         const int p = a < b ? a : b, q = a < b ? b : a;
-        const double app = s_m[p * lp + p], aqq = s_m[q * lp + q], apq = s_m[p * lp + q];
-        double c = 1.0, s = 0.0;
-        if (apq != 0.0) {
-          const double tau = (aqq - app) / (2.0 * apq);
-          const double t = (tau >= 0.0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(1.0 + tau * tau));
-          c = 1.0 / sqrt(1.0 + t * t);
-          s = t * c;
+        const double app = s_m[p * pt + p], aqq = s_m[q * pt + q], apq = s_m[p * pt + q];
+        double c, s, t;
+        jacobi_rot(app, aqq, apq, c, s, t);
+        s_cs[tid] = make_double2(c, s);
+        s_m[p * pt + p] = app - t * apq;
+        s_m[q * pt + q] = aqq + t * apq;
+        s_m[p * pt + q] = 0.0;
+        log[(int64_t)(sweep * (lp - 1) + step) * half + tid] = make_double2(c, s);
+      } else {
+#pragma unroll
+        for (int u = 0; u < 3; ++u) {
+          if (kk[u] < 0) continue;
+          const int k1 = kk[u] & 0xFFFF, k2 = kk[u] >> 16;
+          const int a1 = rr_pos(k1, step, lp), b1 = rr_pos(lp - 1 - k1, step, lp);
+          const int a2 = rr_pos(k2, step, lp), b2 = rr_pos(lp - 1 - k2, step, lp);
+          const int p1 = min(a1, b1), q1 = max(a1, b1), p2 = min(a2, b2), q2 = max(a2, b2);
+          auto ix = [&](int i, int j) { return min(i, j) * pt + max(i, j); };
+          at[u][0] = ix(p1, p2);
+          at[u][1] = ix(p1, q2);
+          at[u][2] = ix(q1, p2);
+          at[u][3] = ix(q1, q2);
+#pragma unroll
+          for (int v = 0; v < 4; ++v) m[u][v] = s_m[at[u][v]];
         }
-        s_p[tid] = p;
-        s_q[tid] = q;
-        s_c[tid] = c;
-        s_s[tid] = s;
       }
-      __syncthreads();
-      // rows: M <- J^T M (rows p, q of every pair, all columns)
-      for (int x = tid; x < half * lp; x += nth) {
-        const int k = x / lp, j = x % lp;
-        const int p = s_p[k], q = s_q[k];
-        const double c = s_c[k], s = s_s[k];
-        const double mp = s_m[p * lp + j], mq = s_m[q * lp + j];
-        s_m[p * lp + j] = c * mp - s * mq;
-        s_m[q * lp + j] = s * mp + c * mq;
+      lds_barrier();
+#pragma unroll
+      for (int u = 0; u < 3; ++u) {
+        if (kk[u] < 0) continue;
+        const double2 e1 = s_cs[kk[u] & 0xFFFF], e2 = s_cs[kk[u] >> 16];
+        const double app = e1.x * m[u][0] - e1.y * m[u][2], aqp = e1.y * m[u][0] + e1.x * m[u][2];
+        const double apq = e1.x * m[u][1] - e1.y * m[u][3], aqq = e1.y * m[u][1] + e1.x * m[u][3];
+        s_m[at[u][0]] = e2.x * app - e2.y * apq;
+        s_m[at[u][1]] = e2.y * app + e2.x * apq;
+        s_m[at[u][2]] = e2.x * aqp - e2.y * aqq;
+        s_m[at[u][3]] = e2.y * aqp + e2.x * aqq;
       }
-      __syncthreads();
-      // columns: M <- M J, and V <- V J
-      for (int x = tid; x < half * lp; x += nth) {
-        const int k = x / lp, i = x % lp;
-        const int p = s_p[k], q = s_q[k];
-        const double c = s_c[k], s = s_s[k];
-        const double mp = s_m[i * lp + p], mq = s_m[i * lp + q];
-        s_m[i * lp + p] = c * mp - s * mq;
-        s_m[i * lp + q] = s * mp + c * mq;
-        const double vp = V[i * lp + p], vq = V[i * lp + q];
-        V[i * lp + p] = c * vp - s * vq;
-        V[i * lp + q] = s * vp + c * vq;
-      }
-      __syncthreads();
+      lds_barrier();
     }
   }
-  // sort descending (ties: lower index first), keep the first l
+  // descending order (ties: lower index first), the first l kept
   if (tid < lp) {
-    const double e = s_m[tid * lp + tid];
+    const double e = s_m[tid * pt + tid];
     int rank = 0;
     for (int j = 0; j < lp; ++j) {
-      const double o = s_m[j * lp + j];
+      const double o = s_m[j * pt + j];
       if (o > e || (o == e && j < tid)) ++rank;
     }
-    s_order[rank] = tid;
+    meta[1 + rank] = tid;
+    if (rank < l) w[rank] = e;
   }
-  __syncthreads();
-  for (int x = tid; x < l * l; x += nth) {
-    const int i = x / l, r = x % l;  // row i of eigenvector column r
-    Vs[x] = V[i * lp + s_order[r]];
+  if (tid == 0) meta[0] = sweep;
+}
+
+// Eigenvectors from k_jacobi's rotation log: row i of V = e_i J_1 J_2 ..., one
+// wavefront per row (the rows are independent), the row in LDS, the log
+// streamed a few steps ahead. Writes row i of the sorted Vs [l][l], and
+// workgroup 0 the singular values (square roots of the r largest eigenvalues).
+constexpr int kJacAhead = 8;
+
+__global__ __launch_bounds__(64) void k_jacobi_vec(const double2* __restrict__ log, const int32_t* __restrict__ meta,
+                                                   int l, int lp, const double* __restrict__ lam, int r,
+                                                   double* __restrict__ Vs, double* __restrict__ sig,
+                                                   double* __restrict__ sigma) {
+  __shared__ double s_v[128];
+  const int lane = threadIdx.x, row = blockIdx.x, half = lp / 2;
+  if (row == 0)
+    for (int i = lane; i < r; i += 64) sig[i] = sigma[i] = sqrt(lam[i] > 0.0 ? lam[i] : 0.0);
+  for (int j = lane; j < lp; j += 64) s_v[j] = j == row ? 1.0 : 0.0;
+  const int nsteps = meta[0] * (lp - 1);
+  const bool on = lane < half;
+  double2 cur[kJacAhead], nxt[kJacAhead];
+  auto fetch = [&](double2* e, int s0) {
+#pragma unroll
+    for (int u = 0; u < kJacAhead; ++u)
+      if (on && s0 + u < nsteps) e[u] = log[(int64_t)(s0 + u) * half + lane];
+  };
+  fetch(cur, 0);
+  int step = 0;  // of the sweep
+  for (int s0 = 0; s0 < nsteps; s0 += kJacAhead) {
+    fetch(nxt, s0 + kJacAhead);
+#pragma unroll
+    for (int u = 0; u < kJacAhead; ++u) {
+      if (s0 + u < nsteps) {
+        if (on) {
+          const int a = rr_pos(lane, step, lp), b = rr_pos(lp - 1 - lane, step, lp);
+          const int p = a < b ? a : b, q = a < b ? b : a;
+          const double vp = s_v[p], vq = s_v[q];
+          s_v[p] = cur[u].x * vp - cur[u].y * vq;
+          s_v[q] = cur[u].y * vp + cur[u].x * vq;
+        }
+        // one wavefront: its LDS accesses execute in order; keep the
+        // compiler from reordering steps
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_wave_barrier();
+        step = step + 1 == lp - 1 ? 0 : step + 1;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < kJacAhead; ++u) cur[u] = nxt[u];
   }
-  if (tid < l) w[tid] = s_m[s_order[tid] * lp + s_order[tid]];
+  for (int j = lane; j < l; j += 64) Vs[(int64_t)row * l + j] = s_v[meta[1 + j]];
 }
 
-// X[i][j] *= sqrt(s[k]) (or /= when invert; 0 where s[k] = 0), k = j
-// (by_col) or i: the symmetric split of the singular values.
-__global__ __launch_bounds__(256) void k_scale(double* __restrict__ X, int rows, int cols, const double* __restrict__ s,
-                                               int by_col, int invert) {
-  const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= (int64_t)rows * cols) return;
-  const int k = by_col ? (int)(q % cols) : (int)(q / cols);
-  const double sg = sqrt(s[k] > 0.0 ? s[k] : 0.0);
-  X[q] = invert ? (sg > 0.0 ? X[q] / sg : 0.0) : X[q] * sg;
-}
-
-__global__ __launch_bounds__(256) void k_sqrt_vec(const double* __restrict__ lam, int n, double* __restrict__ sig) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) sig[i] = sqrt(lam[i] > 0.0 ? lam[i] : 0.0);
-}
-
-__global__ __launch_bounds__(256) void k_copy_f64(const double* __restrict__ x, int n, double* __restrict__ y) {
-  for (int i = threadIdx.x; i < n; i += blockDim.x) y[i] = x[i];
+// The symmetric split of the singular values over a product of S partials
+// [rows][cols]: out = the sum times (by_col) sqrt(s[column]), or divided by
+// sqrt(s[row]) (0 where s is 0), in fp32.
+__global__ __launch_bounds__(256) void k_split_f32(const double* __restrict__ part, int S, int rows, int cols,
+                                                   const double* __restrict__ s, int by_col, float* __restrict__ out) {
+  const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, n = (int64_t)rows * cols;
+  if (q >= n) return;
+  double v = part[q];
+  for (int z = 1; z < S; ++z) v += part[z * n + q];
+  const double x = s[by_col ? (int)(q % cols) : (int)(q / cols)];
+  const double sg = sqrt(x > 0.0 ? x : 0.0);
+  out[q] = (float)(by_col ? v * sg : sg > 0.0 ? v / sg : 0.0);
 }
 
 // Xp = [X; sqrt(damp) I]: rows i < n the activations X [n][cols] (bf16 or
@@ -359,64 +643,121 @@ __global__ __launch_bounds__(256) void k_fill_act(const void* __restrict__ x, in
     Xp[q] = j == i - n ? sd : 0.0;
 }
 
-__global__ __launch_bounds__(256) void k_to_f32(const double* __restrict__ x, int64_t n, float* __restrict__ y) {
-  const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (q < n) y[q] = (float)x[q];
-}
-
 inline unsigned blocks(int64_t n, int t = 256) { return (unsigned)((n + t - 1) / t); }
 
-// Partial tiles for the split products: at most kDgParts doubles.
-constexpr int64_t kDgParts = 384 * DG_T * DG_T;
+// Partial products: at most kDgParts doubles. (The rotation log of k_jacobi
+// takes the same buffer: 40 sweeps of 127 steps of 64 rotations at most.)
+constexpr int64_t kDgParts = 384 * 64 * 64;
+constexpr int kMaxSweeps = 40;
+static_assert((int64_t)kMaxSweeps * 127 * 64 * 2 + 128 <= kDgParts, "the rotation log fits the partial products' buffer");
 
-// C = alpha op(A) op(B). With few output tiles and a long K the K range is
-// split (at least 4 slabs of 16 per split, about 256 workgroups in all) over
-// the partial buffer part (kDgParts doubles, may be null: no split).
-hipError_t dgemm(int M, int N, int K, double alpha, const double* A, int64_t lda, int ta, const double* B, int64_t ldb,
-                 int tb, double* C, int64_t ldc, hipStream_t s, double* part) {
-  if (M <= 0 || N <= 0) return hipSuccess;
-  const int tiles = ((M + DG_T - 1) / DG_T) * ((N + DG_T - 1) / DG_T);
-  int S = 1;
-  if (part && tiles < 128) {
-    S = (256 + tiles - 1) / tiles;
-    const int smax = K / (4 * DG_K);
-    S = S < smax ? S : smax;
-    while (S > 1 && (int64_t)S * M * N > kDgParts) --S;
-    if (S < 1) S = 1;
+constexpr int dg_lds(int mb, int nb) { return 2 * 16 * (mb + nb) * DG_PITCH * 8; }
+
+// The product op(A) op(B) as S > 1 partials [S][M][N] in part (at most `room`
+// doubles), or whole in `one` (S = 1, also where part has no room for two); S
+// returned. Tiles: 64 rows by all N <= 128
+// columns (the sketch-wide products), all M <= 128 rows by 64 columns (their
+// transposes), else 64 x 64; K is split, at least 2 slabs a split and at most
+// max_split ways, so that whole rounds of two workgroups per compute unit (what
+// the LDS holds) share the product: one round for the thin shapes, two for the
+// wide ones.
+template <typename TI>
+int dgemm_parts(int M, int N, int K, const TI* A, int64_t lda, int ta, const TI* B, int64_t ldb, int tb, double* one,
+                double* part, int64_t room, hipStream_t s, int max_split = 1 << 20) {
+  const bool thin_n = N <= 128, thin_m = !thin_n && M <= 128;
+  const int bm = thin_m ? 16 * ((M + 15) / 16) : 64, bn = thin_n ? 16 * ((N + 15) / 16) : 64;
+  const int tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
+  int64_t S = std::max(1, (thin_n || thin_m ? 512 : 1024) / tiles);
+  S = std::min<int64_t>(S, std::min(max_split, K / (2 * DG_K)));
+  S = std::min<int64_t>(S, room / ((int64_t)M * N));
+  S = std::max<int64_t>(S, 1);
+  const int kc = (int)(((K + S - 1) / S + DG_K - 1) / DG_K * DG_K);
+  S = std::max(1, (K + kc - 1) / kc);
+  double* const C = S > 1 ? part : one;
+  const dim3 grid((N + bn - 1) / bn, (M + bm - 1) / bm, (unsigned)S);
+#define LX_DG(WM, WN, MI, NI)                                                                                          \
+  hipLaunchKernelGGL((k_dgemm<TI, WM, WN, MI, NI>), grid, dim3(256), dg_lds(WM * MI, WN * NI), s, M, N, K, A, lda, ta, B, ldb, tb, C,      \
+                     (int64_t)N, kc)
+#define LX_DG_CASES(CASE) CASE(1) CASE(2) CASE(3) CASE(4) CASE(5) CASE(6) CASE(7) CASE(8)
+  if (thin_n) {
+#define LX_CASE(NB) case NB: LX_DG(4, 1, 1, NB); break;
+    switch (bn / 16) { LX_DG_CASES(LX_CASE) }
+#undef LX_CASE
+  } else if (thin_m) {
+#define LX_CASE(NB) case NB: LX_DG(1, 4, NB, 1); break;
+    switch (bm / 16) { LX_DG_CASES(LX_CASE) }
+#undef LX_CASE
+  } else {
+    LX_DG(2, 2, 2, 2);
   }
-  const dim3 grid((N + DG_T - 1) / DG_T, (M + DG_T - 1) / DG_T, S);
-  if (S == 1) {
-    hipLaunchKernelGGL(k_dgemm, grid, dim3(256), 0, s, M, N, K, alpha, A, lda, ta, B, ldb, tb, C, ldc, K);
-    return hipGetLastError();
-  }
-  const int kc = ((K + S - 1) / S + DG_K - 1) / DG_K * DG_K;
-  hipLaunchKernelGGL(k_dgemm, grid, dim3(256), 0, s, M, N, K, alpha, A, lda, ta, B, ldb, tb, part, (int64_t)N, kc);
-  hipLaunchKernelGGL(k_dsum, dim3(blocks((int64_t)M * N)), dim3(256), 0, s, part, S, M, N, C, ldc);
+  return (int)S;
+}
+
+// C [M][N] = op(A) op(B): through the partials when K is split.
+hipError_t dgemm(int M, int N, int K, const double* A, int64_t lda, int ta, const double* B, int64_t ldb, int tb,
+                 double* C, hipStream_t s, double* part) {
+  const int S = dgemm_parts(M, N, K, A, lda, ta, B, ldb, tb, C, part, kDgParts, s);
+  if (S > 1) hipLaunchKernelGGL(k_dsum, dim3(blocks((int64_t)M * N)), dim3(256), 0, s, part, S, (int64_t)M * N, C);
   return hipGetLastError();
 }
 
-// Y (rows x l) <- its orthonormal basis, CholeskyQR2; G, U: l x l scratch.
-// Kernels with up to 128 KB of dynamic LDS: allow it once per process.
+// Kernels with more than 64 KB of dynamic LDS: allow it once per process.
+template <int NB>
+hipError_t allow_lds_nb() {
+  const hipFuncAttribute a = hipFuncAttributeMaxDynamicSharedMemorySize;
+  const int n = 16 * NB * 16 * NB * 8;
+  hipError_t r = hipFuncSetAttribute((const void*)k_chol<NB>, a, n);
+  if (r == hipSuccess) r = hipFuncSetAttribute((const void*)k_trsm_rows<NB>, a, n);
+  if (r == hipSuccess) r = hipFuncSetAttribute((const void*)k_dgemm<double, 4, 1, 1, NB>, a, dg_lds(4, NB));
+  if (r == hipSuccess) r = hipFuncSetAttribute((const void*)k_dgemm<double, 1, 4, NB, 1>, a, dg_lds(NB, 4));
+  if (r == hipSuccess) r = hipFuncSetAttribute((const void*)k_dgemm<float, 4, 1, 1, NB>, a, dg_lds(4, NB));
+  if (r == hipSuccess) r = hipFuncSetAttribute((const void*)k_dgemm<float, 1, 4, NB, 1>, a, dg_lds(NB, 4));
+  return r;
+}
 hipError_t allow_lds() {
   static hipError_t e = [] {
-    const hipFuncAttribute a = hipFuncAttributeMaxDynamicSharedMemorySize;
-    hipError_t r = hipFuncSetAttribute((const void*)k_chol, a, 128 * 1024);
-    if (r == hipSuccess) r = hipFuncSetAttribute((const void*)k_jacobi<false>, a, 128 * 1024);
-    if (r == hipSuccess) r = hipFuncSetAttribute((const void*)k_jacobi<true>, a, 2 * 96 * 96 * 8);
-    if (r == hipSuccess) r = hipFuncSetAttribute((const void*)k_trsm_rows, a, 148 * 1024);
+    hipError_t r = hipFuncSetAttribute((const void*)k_jacobi, hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 129 * 8);
+    if (r == hipSuccess)
+      r = hipFuncSetAttribute((const void*)k_dgemm<double, 2, 2, 2, 2>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                              dg_lds(4, 4));
+    if (r == hipSuccess)
+      r = hipFuncSetAttribute((const void*)k_dgemm<float, 2, 2, 2, 2>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                              dg_lds(4, 4));
+    if (r == hipSuccess) r = allow_lds_nb<1>();
+    if (r == hipSuccess) r = allow_lds_nb<2>();
+    if (r == hipSuccess) r = allow_lds_nb<3>();
+    if (r == hipSuccess) r = allow_lds_nb<4>();
+    if (r == hipSuccess) r = allow_lds_nb<5>();
+    if (r == hipSuccess) r = allow_lds_nb<6>();
+    if (r == hipSuccess) r = allow_lds_nb<7>();
+    if (r == hipSuccess) r = allow_lds_nb<8>();
     return r;
   }();
   return e;
 }
 
-hipError_t cholqr2(double* Y, int rows, int l, double* G, double* U, hipStream_t s, double* part) {
-  for (int pass = 0; pass < 2; ++pass) {
-    hipError_t e = dgemm(l, l, rows, 1.0, Y, l, 1, Y, l, 0, G, l, s, part);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_chol, dim3(1), dim3(1024), (size_t)l * l * sizeof(double), s, G, l, U);
-    const int rw = trsm_rows_per_wg(l);
-    hipLaunchKernelGGL(k_trsm_rows, dim3((rows + rw - 1) / rw), dim3(64), trsm_lds(l), s, Y, rows, l, rw, U);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+// Y (rows x l) <- Y U^-1, U the Cholesky factor of its Gram matrix; U: l x l
+// scratch. One pass gives a basis orthonormal to cond(Y)^2 eps, at most 1e-2
+// under k_chol's pivot floor: enough between the products of the subspace
+// iteration, where only the span and its conditioning count. Two passes
+// (CholeskyQR2) make it orthonormal to rounding, which the final basis is. The
+// Gram matrix's K is split at most 8 ways: k_chol's one workgroup reads the
+// partials.
+hipError_t cholqr(double* Y, int rows, int l, int passes, double* U, hipStream_t s, double* part) {
+  for (int pass = 0; pass < passes; ++pass) {
+    const int S = dgemm_parts(l, l, rows, (const double*)Y, l, 1, (const double*)Y, l, 0, part, part, kDgParts, s, 8);
+    const int nb = (l + 15) / 16;
+    const dim3 gt((rows + kTrsmRows - 1) / kTrsmRows);
+    switch (nb) {
+#define LX_CASE(NB)                                                                                            \
+  case NB:                                                                                                     \
+    hipLaunchKernelGGL(k_chol<NB>, dim3(1), dim3(256), (size_t)l * 16 * NB * 8, s, part, S, l, U);             \
+    hipLaunchKernelGGL(k_trsm_rows<NB>, gt, dim3(256), (size_t)16 * NB * 16 * NB * 8, s, Y, rows, l, U);       \
+    break;
+      LX_DG_CASES(LX_CASE)
+#undef LX_CASE
+    }
+    if (const hipError_t e = hipGetLastError(); e != hipSuccess) return e;
   }
   return hipSuccess;
 }
@@ -425,26 +766,23 @@ hipError_t cholqr2(double* Y, int rows, int l, double* G, double* U, hipStream_t
 // Y^T R (l x cols) and Gm = (Y^T M)(Y^T M)^T (l x l): the eigenpairs of Gm
 // (descending), sigma = the square roots of the r largest, A = Y Ut[:, :r]
 // sigma^(1/2) and B = sigma^(-1/2) Ut[:, :r]^T T (rows of B with sigma = 0
-// are 0); Bd (r x cols doubles) is scratch.
+// are 0); Ad (rows x r) and Bd (r x cols) are scratch.
 hipError_t factors_from_sketch(int rows, int cols, int r, int l, const double* Y, const double* T, const double* Gm,
-                               double* V, double* lam, double* Ve, double* sig, double* Ad, double* Bd, float* A,
-                               float* B, double* sigma, hipStream_t s, double* part) {
-  const int lp = l + (l & 1);
-  if (lp <= 96)
-    hipLaunchKernelGGL(k_jacobi<true>, dim3(1), dim3(1024), 2 * (size_t)lp * lp * sizeof(double), s, Gm, l, lp, V, lam,
-                       Ve, 40);
-  else
-    hipLaunchKernelGGL(k_jacobi<false>, dim3(1), dim3(1024), (size_t)lp * lp * sizeof(double), s, Gm, l, lp, V, lam,
-                       Ve, 40);
-  hipLaunchKernelGGL(k_sqrt_vec, dim3(1), dim3(256), 0, s, lam, r, sig);
-  hipError_t e;
-  if ((e = dgemm(rows, r, l, 1.0, Y, l, 0, Ve, l, 0, Ad, r, s, part)) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_scale, dim3(blocks((int64_t)rows * r)), dim3(256), 0, s, Ad, rows, r, sig, 1, 0);
-  hipLaunchKernelGGL(k_to_f32, dim3(blocks((int64_t)rows * r)), dim3(256), 0, s, Ad, (int64_t)rows * r, A);
-  if ((e = dgemm(r, cols, l, 1.0, Ve, l, 1, T, cols, 0, Bd, cols, s, part)) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_scale, dim3(blocks((int64_t)r * cols)), dim3(256), 0, s, Bd, r, cols, sig, 0, 1);
-  hipLaunchKernelGGL(k_to_f32, dim3(blocks((int64_t)r * cols)), dim3(256), 0, s, Bd, (int64_t)r * cols, B);
-  hipLaunchKernelGGL(k_copy_f64, dim3(1), dim3(256), 0, s, sig, r, sigma);
+                               double* lam, double* Ve, double* sig, double* Ad, double* Bd, float* A, float* B,
+                               double* sigma, hipStream_t s, double* part) {
+  const int lp = l + (l & 1), half = lp / 2;
+  int32_t* const meta = (int32_t*)(part + kDgParts - 128);
+  const int nblk = half * (half - 1) / 2;
+  const int nth = 64 + std::min(960, (nblk + 63) / 64 * 64);  // wavefront 0 and the blocks' threads
+  hipLaunchKernelGGL(k_jacobi, dim3(1), dim3(std::max(nth, 128)), (size_t)lp * (lp + 1) * sizeof(double), s, Gm, l, lp, lam,
+                     (double2*)part, meta, kMaxSweeps);
+  hipLaunchKernelGGL(k_jacobi_vec, dim3(l), dim3(64), 0, s, (const double2*)part, meta, l, lp, lam, r, Ve, sig, sigma);
+  int S = dgemm_parts(rows, r, l, Y, l, 0, (const double*)Ve, l, 0, Ad, part, kDgParts, s);
+  hipLaunchKernelGGL(k_split_f32, dim3(blocks((int64_t)rows * r)), dim3(256), 0, s,
+                     (const double*)(S > 1 ? part : Ad), S, rows, r, sig, 1, A);
+  S = dgemm_parts(r, cols, l, (const double*)Ve, l, 1, T, cols, 0, Bd, part, kDgParts, s);
+  hipLaunchKernelGGL(k_split_f32, dim3(blocks((int64_t)r * cols)), dim3(256), 0, s,
+                     (const double*)(S > 1 ? part : Bd), S, r, cols, sig, 0, B);
   return hipGetLastError();
 }
 
@@ -464,15 +802,20 @@ size_t weighted_ws_doubles(int rows, int cols, int np, int l) {
 
 hipError_t launch_align_cost(const void* dg, const void* du, const void* dd, const void* mg, const void* mu,
                              const void* md, int bf16, int f, int d, double* cost, double* ws, hipStream_t s) {
-  double* const a = ws;
-  double* const b = a + (size_t)f * 3 * d;
-  double* const na = b + (size_t)f * 3 * d;
+  if (const hipError_t e0 = allow_lds(); e0 != hipSuccess) return e0;
+  // ws: 2 f (3d + 1) doubles: the fp32 vectors take half of it, the partial
+  // products the rest
+  const int64_t n = (int64_t)f * 3 * d;
+  float* const a = (float*)ws;
+  float* const b = a + n;
+  double* const na = ws + n;
   double* const nb = na + f;
+  double* const part = nb + f;  // n doubles
   hipLaunchKernelGGL(k_neurons, dim3(f), dim3(256), 0, s, dg, du, dd, bf16, f, d, a, na);
   hipLaunchKernelGGL(k_neurons, dim3(f), dim3(256), 0, s, mg, mu, md, bf16, f, d, b, nb);
-  hipError_t e = dgemm(f, f, 3 * d, 1.0, a, 3 * d, 0, b, 3 * d, 1, cost, f, s, nullptr);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_cost_finish, dim3(blocks((int64_t)f * f)), dim3(256), 0, s, na, nb, f, cost);
+  const int S = dgemm_parts(f, f, 3 * d, (const float*)a, 3 * d, 0, (const float*)b, 3 * d, 1, cost, part, n, s);
+  hipLaunchKernelGGL(k_cost_finish, dim3(blocks((int64_t)f * f)), dim3(256), 0, s, na, nb, f,
+                     (const double*)(S > 1 ? part : cost), S, cost);
   return hipGetLastError();
 }
 
@@ -485,31 +828,30 @@ hipError_t launch_lowrank(const void* wd, const void* wm, int bf16, int rows, in
   double* const Y = R + (size_t)rows * cols;         // rows x l
   double* const Z = Y + (size_t)rows * l;            // cols x l
   double* const Bs = Z + (size_t)cols * l;           // l x cols
-  double* const G = Bs + (size_t)l * cols;           // lp x lp (four of them)
+  double* const G = Bs + (size_t)l * cols;           // lp x lp (three of them)
   double* const U = G + (size_t)lp * lp;
-  double* const V = U + (size_t)lp * lp;
-  double* const Ve = V + (size_t)lp * lp;
+  double* const Ve = U + (size_t)lp * lp;
   double* const lam = Ve + (size_t)lp * lp;          // lp
   double* const sig = lam + lp;                      // lp
   double* const Ad = sig + lp;                       // rows x l (A before truncation)
-  double* const part = Ad + (size_t)rows * l;        // kDgParts (split-K partial tiles)
+  double* const part = Ad + (size_t)rows * l;        // kDgParts (partial products)
   hipLaunchKernelGGL(k_residual, dim3(blocks((int64_t)rows * cols)), dim3(256), 0, s, wd, wm, bf16, rows, cols, perm,
                      axis, R);
   hipError_t e;
   // Y = R Omega, orthonormalised; q rounds of Z = R^T Y, Y = R Z, each
   // orthonormalised
-  if ((e = dgemm(rows, l, cols, 1.0, R, cols, 0, omega, l, 0, Y, l, s, part)) != hipSuccess) return e;
-  if ((e = cholqr2(Y, rows, l, G, U, s, part)) != hipSuccess) return e;
+  if ((e = dgemm(rows, l, cols, R, cols, 0, omega, l, 0, Y, s, part)) != hipSuccess) return e;
+  if ((e = cholqr(Y, rows, l, q > 0 ? 1 : 2, U, s, part)) != hipSuccess) return e;
   for (int it = 0; it < q; ++it) {
-    if ((e = dgemm(cols, l, rows, 1.0, R, cols, 1, Y, l, 0, Z, l, s, part)) != hipSuccess) return e;
-    if ((e = cholqr2(Z, cols, l, G, U, s, part)) != hipSuccess) return e;
-    if ((e = dgemm(rows, l, cols, 1.0, R, cols, 0, Z, l, 0, Y, l, s, part)) != hipSuccess) return e;
-    if ((e = cholqr2(Y, rows, l, G, U, s, part)) != hipSuccess) return e;
+    if ((e = dgemm(cols, l, rows, R, cols, 1, Y, l, 0, Z, s, part)) != hipSuccess) return e;
+    if ((e = cholqr(Z, cols, l, 1, U, s, part)) != hipSuccess) return e;
+    if ((e = dgemm(rows, l, cols, R, cols, 0, Z, l, 0, Y, s, part)) != hipSuccess) return e;
+    if ((e = cholqr(Y, rows, l, it + 1 < q ? 1 : 2, U, s, part)) != hipSuccess) return e;
   }
   // Bs = Y^T R (l x cols); Bs Bs^T (l x l) = Ut diag(lambda) Ut^T
-  if ((e = dgemm(l, cols, rows, 1.0, Y, l, 1, R, cols, 0, Bs, cols, s, part)) != hipSuccess) return e;
-  if ((e = dgemm(l, l, cols, 1.0, Bs, cols, 0, Bs, cols, 1, G, l, s, part)) != hipSuccess) return e;
-  return factors_from_sketch(rows, cols, r, l, Y, Bs, G, V, lam, Ve, sig, Ad, Z, A, B, sigma, s, part);
+  if ((e = dgemm(l, cols, rows, Y, l, 1, R, cols, 0, Bs, s, part)) != hipSuccess) return e;
+  if ((e = dgemm(l, l, cols, Bs, cols, 0, Bs, cols, 1, G, s, part)) != hipSuccess) return e;
+  return factors_from_sketch(rows, cols, r, l, Y, Bs, G, lam, Ve, sig, Ad, Z, A, B, sigma, s, part);
 }
 
 hipError_t launch_weighted(const void* wd, const void* wm, int bf16, int rows, int cols, const int32_t* perm, int axis,
@@ -525,10 +867,9 @@ hipError_t launch_weighted(const void* wd, const void* wm, int bf16, int rows, i
   double* const Z = Y + (size_t)rows * l;            // np x l
   double* const T = Z + (size_t)np * l;              // l x cols
   double* const Wt = T + (size_t)l * cols;           // l x np
-  double* const G = Wt + (size_t)l * np;             // lp x lp (four of them)
+  double* const G = Wt + (size_t)l * np;             // lp x lp (three of them)
   double* const U = G + (size_t)lp * lp;
-  double* const V = U + (size_t)lp * lp;
-  double* const Ve = V + (size_t)lp * lp;
+  double* const Ve = U + (size_t)lp * lp;
   double* const lam = Ve + (size_t)lp * lp;          // lp
   double* const sig = lam + lp;                      // lp
   double* const Ad = sig + lp;                       // rows x l
@@ -541,23 +882,23 @@ hipError_t launch_weighted(const void* wd, const void* wm, int bf16, int rows, i
   // The operator M = R Xp^T (rows x np), applied as two thin products:
   // Y = R (Xp^T Omega), orthonormalised; q rounds of Z = Xp (R^T Y) and
   // Y = R (Xp^T Z), each orthonormalised
-  if ((e = dgemm(cols, l, np, 1.0, Xp, cols, 1, omega, l, 0, P, l, s, part)) != hipSuccess) return e;
-  if ((e = dgemm(rows, l, cols, 1.0, R, cols, 0, P, l, 0, Y, l, s, part)) != hipSuccess) return e;
-  if ((e = cholqr2(Y, rows, l, G, U, s, part)) != hipSuccess) return e;
+  if ((e = dgemm(cols, l, np, Xp, cols, 1, omega, l, 0, P, s, part)) != hipSuccess) return e;
+  if ((e = dgemm(rows, l, cols, R, cols, 0, P, l, 0, Y, s, part)) != hipSuccess) return e;
+  if ((e = cholqr(Y, rows, l, q > 0 ? 1 : 2, U, s, part)) != hipSuccess) return e;
   for (int it = 0; it < q; ++it) {
-    if ((e = dgemm(cols, l, rows, 1.0, R, cols, 1, Y, l, 0, P, l, s, part)) != hipSuccess) return e;
-    if ((e = dgemm(np, l, cols, 1.0, Xp, cols, 0, P, l, 0, Z, l, s, part)) != hipSuccess) return e;
-    if ((e = cholqr2(Z, np, l, G, U, s, part)) != hipSuccess) return e;
-    if ((e = dgemm(cols, l, np, 1.0, Xp, cols, 1, Z, l, 0, P, l, s, part)) != hipSuccess) return e;
-    if ((e = dgemm(rows, l, cols, 1.0, R, cols, 0, P, l, 0, Y, l, s, part)) != hipSuccess) return e;
-    if ((e = cholqr2(Y, rows, l, G, U, s, part)) != hipSuccess) return e;
+    if ((e = dgemm(cols, l, rows, R, cols, 1, Y, l, 0, P, s, part)) != hipSuccess) return e;
+    if ((e = dgemm(np, l, cols, Xp, cols, 0, P, l, 0, Z, s, part)) != hipSuccess) return e;
+    if ((e = cholqr(Z, np, l, 1, U, s, part)) != hipSuccess) return e;
+    if ((e = dgemm(cols, l, np, Xp, cols, 1, Z, l, 0, P, s, part)) != hipSuccess) return e;
+    if ((e = dgemm(rows, l, cols, R, cols, 0, P, l, 0, Y, s, part)) != hipSuccess) return e;
+    if ((e = cholqr(Y, rows, l, it + 1 < q ? 1 : 2, U, s, part)) != hipSuccess) return e;
   }
   // T = Y^T R (l x cols); Wt = Y^T M = T Xp^T (l x np); Wt Wt^T = Ut diag(lambda) Ut^T.
   // B = sigma^(-1/2) Ut^T T is sigma^(-1/2) U_r^T R with U_r = Y Ut[:, :r].
-  if ((e = dgemm(l, cols, rows, 1.0, Y, l, 1, R, cols, 0, T, cols, s, part)) != hipSuccess) return e;
-  if ((e = dgemm(l, np, cols, 1.0, T, cols, 0, Xp, cols, 1, Wt, np, s, part)) != hipSuccess) return e;
-  if ((e = dgemm(l, l, np, 1.0, Wt, np, 0, Wt, np, 1, G, l, s, part)) != hipSuccess) return e;
-  return factors_from_sketch(rows, cols, r, l, Y, T, G, V, lam, Ve, sig, Ad, P, A, B, sigma, s, part);
+  if ((e = dgemm(l, cols, rows, Y, l, 1, R, cols, 0, T, s, part)) != hipSuccess) return e;
+  if ((e = dgemm(l, np, cols, T, cols, 0, Xp, cols, 1, Wt, s, part)) != hipSuccess) return e;
+  if ((e = dgemm(l, l, np, Wt, np, 0, Wt, np, 1, G, s, part)) != hipSuccess) return e;
+  return factors_from_sketch(rows, cols, r, l, Y, T, G, lam, Ve, sig, Ad, P, A, B, sigma, s, part);
 }
 
 }  // namespace lx

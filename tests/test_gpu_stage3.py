@@ -171,3 +171,60 @@ def test_weighted_factors_pure_damping_is_the_plain_fit():
     Aw, Bw, Ap, Bp = (t.cpu().numpy().astype(np.float64) for t in (Aw, Bw, Ap, Bp))
     assert np.allclose(sw.cpu().numpy(), np.sqrt(damp) * sp.cpu().numpy(), rtol=1e-10)
     assert _rel(Aw @ Bw, Ap @ Bp) <= 1e-5
+
+
+@pytest.mark.parametrize("rows,cols,r,p", [(17, 33, 1, 0), (64, 64, 16, 0), (65, 200, 15, 2), (130, 97, 64, 33),
+                                           (97, 300, 97, 0), (200, 131, 98, 13), (128, 128, 120, 8),
+                                           (129, 1000, 128, 0)])
+def test_factors_at_the_sketch_width_edges(rows, cols, r, p):
+    """Sketch widths around the 16-column blocks of the fp64 kernels, odd and
+    even (padded Jacobi), up to 128, and product edges that are no multiples of
+    the 64-row tiles. sigma: the eigenvalues of the Gram matrix are good to a
+    few rows * eps * sigma_1^2."""
+    require_gpu()
+    say(f"stage 3 widths rows={rows} cols={cols} r={r} p={p}")
+    rng = np.random.default_rng(rows * 1000 + r)
+    wd = rng.standard_normal((rows, cols)).astype(np.float32)
+    low = rng.standard_normal((rows, r)) * np.exp(-0.02 * np.arange(r)) @ rng.standard_normal((r, cols))
+    wm = (wd + 0.1 * low + 0.01 * rng.standard_normal((rows, cols))).astype(np.float32)
+    om = rng.standard_normal((cols, r + p))
+    A, B, sig = lx.lowrank_factors(torch.from_numpy(wd).cuda(), torch.from_numpy(wm).cuda(), r,
+                                   torch.from_numpy(om).cuda(), q=2)
+    A, B, sig = A.cpu().numpy().astype(np.float64), B.cpu().numpy().astype(np.float64), sig.cpu().numpy()
+    A0, B0, s0 = S.factors(wm.astype(np.float64) - wd, om, r, q=2)
+    assert _rel(A @ B, A0 @ B0) <= 1e-6
+    assert np.all(np.abs(sig - s0) <= 64 * rows * 2.3e-16 * s0[0] ** 2 / s0)
+    assert np.all(np.diff(sig) <= 0)
+
+
+def test_factors_of_an_exactly_low_rank_residual():
+    """More sketch columns than the residual's rank: the columns it does not
+    have carry nothing, and A B is the residual."""
+    require_gpu()
+    rng = np.random.default_rng(5)
+    rows, cols, true = 150, 260, 11
+    R = (rng.integers(-8, 9, (rows, true)) @ rng.integers(-8, 9, (true, cols))).astype(np.float32)
+    wd = rng.integers(-64, 65, (rows, cols)).astype(np.float32)
+    om = rng.standard_normal((cols, 42))
+    A, B, sig = lx.lowrank_factors(torch.from_numpy(wd).cuda(), torch.from_numpy(wd + R).cuda(), 32,
+                                   torch.from_numpy(om).cuda(), q=2)
+    A, B, sig = A.cpu().numpy().astype(np.float64), B.cpu().numpy().astype(np.float64), sig.cpu().numpy()
+    assert _rel(A @ B, R) <= 1e-6
+    # noise eigenvalues: rows * eps * sigma_1^2 at most
+    assert np.all(sig[true:] <= np.sqrt(64 * rows * 2.3e-16) * sig[0])
+
+
+@pytest.mark.parametrize("f,d,dtype", [(1, 8, "f32"), (63, 24, "f32"), (130, 40, "bf16"), (200, 8, "bf16")])
+def test_align_cost_edges(f, d, dtype):
+    """Cost matrices off the 64-wide tiles, with and without a split K."""
+    require_gpu()
+    rng = np.random.default_rng(f)
+    w = [rng.standard_normal(s).astype(np.float32) for s in ((f, d), (f, d), (d, f)) * 2]
+    if dtype == "bf16":
+        w = [_bf(v) for v in w]
+        dev = [_dev(v) for v in w]
+    else:
+        dev = [torch.from_numpy(v).cuda() for v in w]
+    got = lx.align_cost(tuple(dev[:3]), tuple(dev[3:])).cpu().numpy()
+    ref = S.align_cost(w[:3], w[3:], dtype)
+    assert np.max(np.abs(got - ref)) <= 1e-12 * np.max(np.abs(ref))

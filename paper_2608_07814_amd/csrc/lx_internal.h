@@ -43,10 +43,12 @@ __device__ __forceinline__ uint4 x16_pack8(float4 a, float4 b) {
   return make_uint4(pk(a.x, a.y, 0), pk(a.z, a.w, 1), pk(b.x, b.y, 2), pk(b.z, b.w, 3));
 }
 
-// the group's exponent byte from its slots' low bits
+// the group's exponent byte from its slots' low bits: bits 0 and 16 of word i
+// go to bits 2i and 16 + 2i, then the odd bits fold in
 __device__ __forceinline__ uint32_t x16_exp8(const uint4& w) {
-  return (w.x & 1u) | ((w.x >> 15) & 2u) | ((w.y & 1u) << 2) | ((w.y >> 13) & 8u) | ((w.z & 1u) << 4) |
-         ((w.z >> 11) & 32u) | ((w.w & 1u) << 6) | ((w.w >> 9) & 128u);
+  const uint32_t m = 0x10001u;
+  const uint32_t t = (w.x & m) | ((w.y & m) << 2) | ((w.z & m) << 4) | ((w.w & m) << 6);
+  return (t | (t >> 15)) & 0xFFu;
 }
 
 // values 4 h .. 4 h + 3 of a group (h = 0 or 1)

@@ -124,6 +124,23 @@ def test_rank_not_multiple_of_64(cfg, over, T):
     assert e <= TOL_BF16 and e <= TOL_DESIGN
 
 
+@pytest.mark.parametrize("over,T", [({}, 160), ({}, 257), ({}, 450), ({"f": 320}, 700), ({"r": 96, "f": 192}, 300),
+                                    ({"E": 32, "C": 2, "k": 4, "f": 192}, 640), ({"E": 64, "C": 32}, 300)])
+def test_mid_sized_batches_on_every_tile_shape(over, T):
+    """Batches between the skinny kernel's and the full 256 x 256 grid's: the
+    bf16 products run on 128 x 64, 128 x 128, 256 x 128 and 256 x 256 tiles,
+    with ragged rows per node, a rank that wraps within a K slab and column
+    counts that are no multiple of the tile."""
+    require_gpu()
+    cfg = dict(config(1, d=512, f=256), **over)
+    p = make_problem(cfg, seed=T, T=T)
+    ref = _oracle(p)
+    for kw in (dict(), dict(f16=False), dict(f16=False, lo8=False)):
+        e = err_ratio(gpu_forward(p, dev_layer=lx.to_device(p.layer, **kw)), ref)
+        say(f"mid-sized {over} T={T} {kw}: err/RMS = {e:.3e}")
+        assert e <= TOL_BF16 and e <= TOL_DESIGN
+
+
 def test_cfg4_tree_small():
     require_gpu()
     say("forward cfg4 T=8")

@@ -81,6 +81,19 @@ def test_lo8_forward_vs_oracle_and_bf16_pair(cfg, T):
     assert e8 <= TOL_DESIGN
 
 
+def test_lo8_is_taken_where_256_row_tiles_fill_the_chip():
+    """16 anchors x 3 row tiles x 8 column tiles: the fp8 lo half runs (its
+    result differs from the bf16 pair's); both meet the bar."""
+    require_gpu()
+    from lxsynth import config
+    p = make_problem(config(1, f=320), T=1600)
+    ref = O.moe_forward(p.layer, p.x, p.routing.topk_ids, p.routing.topk_weights)
+    g8 = gpu_forward(p, dev_layer=lx.to_device(p.layer, lo8=True, f16=False))
+    g16 = gpu_forward(p, dev_layer=lx.to_device(p.layer, lo8=False, f16=False))
+    assert not np.array_equal(g8, g16)
+    assert err_ratio(g8, ref) <= TOL_DESIGN and err_ratio(g16, ref) <= TOL_DESIGN
+
+
 def test_lo8_dense_comparator():
     require_gpu()
     from lxsynth import make_layer_flat

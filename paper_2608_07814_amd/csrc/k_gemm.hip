@@ -16,7 +16,8 @@
 //     distinct banks;
 //   * double-buffered LDS with register prefetch: the next K-slab is loaded
 //     from HBM while the current one is multiplied.
-// fp32 path: a plain LDS-tiled VALU kernel (fp32 layers are small).
+// fp32 path: v_mfma_f32_32x32x2_f32 on 64 x 64 tiles with direct HBM -> LDS loads
+// (K a multiple of 16), else a plain LDS-tiled VALU kernel.
 #include "lx_internal.h"
 
 namespace lx {
@@ -283,6 +284,130 @@ __global__ __launch_bounds__(256) void k_gemm_f32(GemmArgs p) {
   }
 }
 
+// The fp32 products on the matrix cores: 64 x 64 tiles by 4 wavefronts (2 x 2
+// grid of 32 x 32 blocks), full fp32 operands and accumulation (in two sums of
+// half the products each, which also halves the rounding of one long chain).
+// K slabs of MBK values go straight to LDS through a ring of MST stages; 48 KB
+// per workgroup (32 KB when MBK is 16), so three or more workgroups share a
+// compute unit and cover each other's waits. LDS rows of MBK values, 16-byte
+// chunks XOR-swizzled by the row so that 16 rows of one chunk fall on distinct
+// banks. A lane's 16-byte fragment read holds 4 consecutive k of its row; the two
+// lane halves read neighbouring chunks, so MFMA step s of a chunk pair multiplies
+// k = s and k = 4 + s (any pairing sums the same products). Bound by the fp32
+// MFMA rate (157 TFLOP/s nominal) and padding rows. Against the VALU kernel
+// above: d = 2048, f = 768, 16 anchors, rank 64, T = 300: anchor gate|up 405 -> 187
+// us (two thirds of it MFMA time), low-rank input 318 -> 60, anchor down 180 ->
+// 90. 128-column tiles: 177, 96, 104; 16-wide slabs: 191, 73, 97.
+__device__ __forceinline__ void f32_load_lds16(const void* gptr, const void* lds_dst) {
+  typedef __attribute__((address_space(3))) void lds_void_t;
+  const uint32_t lds = (uint32_t)(uintptr_t)(lds_void_t*)lds_dst;
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
+               :
+               : "v"(gptr), "s"(__builtin_amdgcn_readfirstlane(lds))
+               : "memory");
+}
+// s_waitcnt vmcnt(N) alone; barrier without a fence (each wavefront waits for
+// its own loads first)
+template <int N>
+__device__ __forceinline__ void f32_wait_vm() {
+  __builtin_amdgcn_s_waitcnt((N & 0xF) | ((N >> 4) << 14) | (0x7 << 4) | (0xF << 8));
+}
+__device__ __forceinline__ void f32_bar() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+template <int MBK, int MST>
+__global__ __launch_bounds__(256) void k_gemm_f32m(GemmArgs p) {
+  constexpr int CH = MBK / 4, RPT = 256 / CH;  // 16-byte chunks per row, rows per load round
+  constexpr int RA = FBM / RPT, RB = FBN / RPT;
+  // XCD-aware order (workgroups go round-robin over the 8 XCDs): each XCD takes
+  // a contiguous range of (row tile, column tile) items, so the column tiles of
+  // a row tile and the row tiles of a node share rows and weights in one L2
+  const int ntp0 = (p.ncols[0] + FBN - 1) / FBN, ntn = ntp0 + (p.ncols[1] + FBN - 1) / FBN;
+  const int items = *p.n_tiles * ntn, x = blockIdx.x % 8, q8 = items / 8, r8 = items % 8;
+  const int in_xcd = blockIdx.x / 8;
+  if (in_xcd >= q8 + (x < r8 ? 1 : 0)) return;
+  const int item = x * q8 + (x < r8 ? x : r8) + in_xcd;
+  const TileEntry te = p.tiles[item / ntn];
+  const int nt = item % ntn, part = nt < ntp0 ? 0 : 1;
+  const int n0 = (nt - (part ? ntp0 : 0)) * FBN;
+  const int ncol = p.ncols[part];
+  const int K = p.K;
+  __shared__ __attribute__((aligned(1024))) float smem[MST * (FBM + FBN) * MBK];
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+
+  // rows past the tile's end and weight rows past ncol are clamped (their
+  // results are never stored), so every load is in bounds
+  auto swz = [](int row) { return MBK == 16 ? (row >> 2) & 3 : (row >> 1) & 7; };
+  const float* ap[RA];
+  const float* bp[RB];
+#pragma unroll
+  for (int i = 0; i < RA; ++i) {
+    const int row = i * RPT + tid / CH, c = (tid % CH) ^ swz(row);
+    const int r = row < te.nrows ? row : te.nrows - 1;
+    const int64_t src = p.a_rows ? (int64_t)p.a_rows[te.row0 + r] : (int64_t)(te.row0 + r);
+    ap[i] = (const float*)p.A + src * p.lda + p.a_koff[part] + c * 4;
+  }
+#pragma unroll
+  for (int i = 0; i < RB; ++i) {
+    const int row = i * RPT + tid / CH, c = (tid % CH) ^ swz(row);
+    const int n = n0 + row < ncol ? n0 + row : ncol - 1;
+    bp[i] = (const float*)p.B[part] + (int64_t)te.widx * p.b_stride[part] + (int64_t)n * K + c * 4;
+  }
+  auto issue = [&](int kt) {
+    float* const st = smem + (kt % MST) * (FBM + FBN) * MBK;
+#pragma unroll
+    for (int i = 0; i < RA; ++i) f32_load_lds16(ap[i] + kt * MBK, st + i * 1024 + wave * 256);
+#pragma unroll
+    for (int i = 0; i < RB; ++i) f32_load_lds16(bp[i] + kt * MBK, st + FBM * MBK + i * 1024 + wave * 256);
+  };
+
+  const int wm = wave >> 1, wn = wave & 1, half = lane >> 5;
+  const int ra = wm * 32 + (lane & 31), rb = wn * 32 + (lane & 31);
+  const bool live = wm * 32 < te.nrows && n0 + wn * 32 < ncol;  // wavefront-uniform
+  f32x16 acc0, acc1;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) acc0[i] = acc1[i] = 0.f;
+  const int nk = K / MBK;
+  const int npre = nk < MST - 1 ? nk : MST - 1;
+  for (int i = 0; i < npre; ++i) issue(i);
+  for (int kt = 0; kt < nk; ++kt) {
+    // slabs issued so far: 0 .. min(kt + MST - 2, nk - 1); slab kt must have landed
+    const int ahead = (kt + MST - 2 < nk - 1 ? kt + MST - 2 : nk - 1) - kt;
+    if (ahead >= 2)
+      f32_wait_vm<2 * (RA + RB)>();
+    else if (ahead == 1)
+      f32_wait_vm<RA + RB>();
+    else
+      f32_wait_vm<0>();
+    f32_bar();  // slab kt is in LDS; slab kt - 1's stage is free
+    if (kt + MST - 1 < nk) issue(kt + MST - 1);
+    if (live) {
+      const float* const st = smem + (kt % MST) * (FBM + FBN) * MBK;
+#pragma unroll
+      for (int j = 0; j < CH / 2; ++j) {
+        const int c = 2 * j + half;
+        const float4 fa = *(const float4*)(st + ra * MBK + ((c ^ swz(ra)) << 2));
+        const float4 fb = *(const float4*)(st + FBM * MBK + rb * MBK + ((c ^ swz(rb)) << 2));
+        acc0 = __builtin_amdgcn_mfma_f32_32x32x2f32(fa.x, fb.x, acc0, 0, 0, 0);
+        acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(fa.y, fb.y, acc1, 0, 0, 0);
+        acc0 = __builtin_amdgcn_mfma_f32_32x32x2f32(fa.z, fb.z, acc0, 0, 0, 0);
+        acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(fa.w, fb.w, acc1, 0, 0, 0);
+      }
+    }
+  }
+  const int c = n0 + wn * 32 + (lane & 31);
+  if (!live || c >= ncol) return;
+  float* __restrict__ C = p.C + p.c_coloff[part] + c;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int rr = wm * 32 + 8 * (i >> 2) + 4 * half + (i & 3);
+    if (rr < te.nrows) C[(int64_t)(te.row0 + rr) * p.ldc] = acc0[i] + acc1[i];
+  }
+}
+
 }  // namespace
 
 int gemm_bm(lx_dtype dt) { return dt == LX_BF16 ? BM : FBM; }
@@ -294,7 +419,17 @@ hipError_t launch_gemm(const GemmArgs& g, lx_dtype dt, AMode am, int grid_x, hip
   if (grid_x <= 0 || gy <= 0) return hipSuccess;
   const dim3 grid(grid_x, gy);
   if (dt == LX_F32) {
-    hipLaunchKernelGGL(k_gemm_f32, grid, dim3(256), 0, s, g);
+    // 16-byte loads of whole slabs: K, the row pitch and every column offset
+    // multiples of 4 values (weights and workspace are 16-byte aligned)
+    const bool ok = g.lda % 4 == 0 && g.a_koff[0] % 4 == 0 && g.a_koff[1] % 4 == 0 && g.b_stride[0] % 4 == 0 &&
+                    g.b_stride[1] % 4 == 0;
+    const dim3 wgs((unsigned)(((int64_t)grid_x * gy + 7) / 8 * 8));
+    if (ok && g.K % 32 == 0)
+      hipLaunchKernelGGL((k_gemm_f32m<32, 3>), wgs, dim3(256), 0, s, g);
+    else if (ok && g.K % 16 == 0)
+      hipLaunchKernelGGL((k_gemm_f32m<16, 4>), wgs, dim3(256), 0, s, g);
+    else
+      hipLaunchKernelGGL(k_gemm_f32, grid, dim3(256), 0, s, g);
   } else if (am == A_BF16) {
     hipLaunchKernelGGL(k_gemm_bf16<A_BF16>, grid, dim3(NTHR), 0, s, g);
   } else {

@@ -141,6 +141,19 @@ def test_mid_sized_batches_on_every_tile_shape(over, T):
         assert e <= TOL_BF16 and e <= TOL_DESIGN
 
 
+@pytest.mark.parametrize("over,T", [({"d": 512, "f": 256, "r": 64}, 65), ({"d": 96, "f": 80, "r": 16}, 130),
+                                    ({"d": 72, "f": 104, "r": 12}, 40), ({"d": 256, "f": 128, "r": 5}, 1),
+                                    ({"d": 64, "f": 32, "r": 48}, 300)])
+def test_fp32_products_at_their_edges(over, T):
+    """fp32 layers: K slabs of 32, of 16 and neither (the VALU kernel), a
+    rank off both, rows and columns off the 64-wide tiles."""
+    require_gpu()
+    p = make_problem(dict(config(1, dtype="f32"), **over), seed=T, T=T)
+    e = err_ratio(gpu_forward(p), _oracle(p))
+    say(f"fp32 {over} T={T}: err/RMS = {e:.3e}")
+    assert e <= TOL_F32
+
+
 def test_cfg4_tree_small():
     require_gpu()
     say("forward cfg4 T=8")

@@ -4,13 +4,13 @@
 // choice. They run once per layer on calibration routing and fix the
 // cluster map and factor indices of a flat layer.
 //
-//   * k_coact: one thread per calibration token; an expert fires on a token
-//     when it is among the token's valid ids (once per token); every
-//     unordered pair of distinct firing experts co-fires once. Integer
-//     atomics (order-free, so the counts are exact and reproducible); for
-//     E <= 128 the counts of a workgroup's tokens are gathered in LDS first
-//     and only the non-zero ones go to global memory.
-//   * k_npmi: D = 1 - NPMI in fp64, one thread per (i, j).
+//   * k_coact: an expert fires on a token when it is among the token's valid
+//     ids (once per token); every unordered pair of distinct firing experts
+//     co-fires once. E <= 128: per 1024 tokens one bit mask per expert in LDS;
+//     the counts are the popcounts of the masks' pairwise intersections, kept
+//     in registers over a workgroup's tokens and added to global memory once.
+//     Else integer atomics per token. Order-free either way, so exact.
+//   * k_npmi: D = 1 - NPMI in fp64, one thread per (i, j); mirrors the counts.
 //   * k_kmedoids: one workgroup, one thread per expert (E <= 1024). Seeds =
 //     the highest-firing unprotected experts; assign (nearest medoid, ties to
 //     the lower cluster, a medoid stays in its own cluster) / update (member
@@ -20,14 +20,18 @@
 //     decision is the exact fp64 comparison a sequential loop would make.
 #include "lx_internal.h"
 
+#include <algorithm>
+
 namespace lx {
 namespace {
 
 constexpr int KM_THR = 1024;
 
-__global__ __launch_bounds__(256) void k_fill_u32(uint32_t* __restrict__ p, int64_t n) {
+__global__ __launch_bounds__(256) void k_fill2_u32(uint32_t* __restrict__ p, int64_t n, uint32_t* __restrict__ q,
+                                                   int64_t m) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = 0u;
+  if (i < m) q[i] = 0u;
 }
 
 // Valid, first-occurrence ids of token t: slot j counts when 0 <= id < E and
@@ -40,47 +44,99 @@ __device__ __forceinline__ bool first_valid(const int32_t* row, int j, int E) {
   return true;
 }
 
-template <bool LDS>
+// One thread per token, integer atomics on global memory (any E).
 __global__ __launch_bounds__(256) void k_coact(const int32_t* __restrict__ ids, int N, int k, int E,
                                                uint32_t* __restrict__ fire, uint32_t* __restrict__ pair) {
-  __shared__ uint32_t s_pair[LDS ? 128 * 128 : 1];
-  __shared__ uint32_t s_fire[LDS ? 128 : 1];
-  if (LDS) {
-    for (int i = threadIdx.x; i < E * E; i += blockDim.x) s_pair[i] = 0u;
-    for (int i = threadIdx.x; i < E; i += blockDim.x) s_fire[i] = 0u;
-    __syncthreads();
-  }
   for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < N; t += gridDim.x * blockDim.x) {
     const int32_t* row = ids + (int64_t)t * k;
     for (int a = 0; a < k; ++a) {
       if (!first_valid(row, a, E)) continue;
       const int ea = row[a];
-      if (LDS)
-        atomicAdd(&s_fire[ea], 1u);
-      else
-        atomicAdd(&fire[ea], 1u);
+      atomicAdd(&fire[ea], 1u);
       for (int b = a + 1; b < k; ++b) {
         if (!first_valid(row, b, E)) continue;
         const int eb = row[b];
         const int lo = ea < eb ? ea : eb, hi = ea < eb ? eb : ea;
-        if (LDS)
-          atomicAdd(&s_pair[lo * E + hi], 1u);
-        else
-          atomicAdd(&pair[(int64_t)lo * E + hi], 1u);
+        atomicAdd(&pair[(int64_t)lo * E + hi], 1u);
       }
     }
   }
-  if (LDS) {
-    __syncthreads();
-    for (int i = threadIdx.x; i < E * E; i += blockDim.x)
-      if (s_pair[i]) atomicAdd(&pair[i], s_pair[i]);
-    for (int i = threadIdx.x; i < E; i += blockDim.x)
-      if (s_fire[i]) atomicAdd(&fire[i], s_fire[i]);
-  }
 }
 
-// Counts were gathered in the upper triangle: mirror it and zero the diagonal,
-// then D = 1 - NPMI.
+// E <= 128: 1024 tokens at a time, a 1024-bit mask per expert in LDS (a repeated
+// id sets its bit once). A thread owns the pairs (bi + 32 u, bj + 32 v), u, v < 4,
+// of one bi <= bj < 32 (528 threads; neighbouring threads read neighbouring
+// experts' masks, on distinct banks), and counts popcount(mask_i & mask_j) in
+// registers; the diagonal gives the firing counts.
+// What bounds it is the final adds to global memory (about 37 per ns over the
+// chip), so kCoactGroups workgroups share the tokens. Against the kernel that
+// gathered pair counts in LDS and flushed them per 256 tokens: 131072 tokens,
+// top-8, E = 128: 78 -> 35 us.
+constexpr int kCoactTok = 1024, kCoactThr = 1024, kCoactGroups = 64, kCoactPitch = kCoactTok / 32 + 4;
+
+__global__ __launch_bounds__(kCoactThr) void k_coact_bits(const int32_t* __restrict__ ids, int N, int k, int E,
+                                                          uint32_t* __restrict__ fire, uint32_t* __restrict__ pair) {
+  // (pitch: 16-byte aligned rows, an odd number of 16-byte chunks)
+  __shared__ __attribute__((aligned(16))) uint32_t s_mask[128 * kCoactPitch];
+  const int tid = threadIdx.x;
+  int bi = 0, bj = tid;  // block pair of this thread
+  while (bi < 32 && bj >= 32 - bi) {
+    bj -= 32 - bi;
+    ++bi;
+  }
+  bj += bi;
+  const bool own = bi < 32 && bi < E && bj < E;
+  uint32_t cnt[4][4] = {};
+  for (int t0 = blockIdx.x * kCoactTok; t0 < N; t0 += gridDim.x * kCoactTok) {
+    for (int i = tid; i < 128 * kCoactPitch; i += kCoactThr) s_mask[i] = 0u;
+    __syncthreads();
+    const int t = t0 + tid;
+    if (t < N) {
+      const int32_t* row = ids + (int64_t)t * k;
+      for (int a0 = 0; a0 < k; a0 += 8) {
+        int e[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) e[u] = row[a0 + u < k ? a0 + u : k - 1];  // (a repeat changes nothing)
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+          if (e[u] >= 0 && e[u] < E) atomicOr(&s_mask[e[u] * kCoactPitch + (tid >> 5)], 1u << (tid & 31));
+      }
+    }
+    __syncthreads();
+    if (own) {
+      for (int w = 0; w < kCoactTok / 32; w += 4) {
+        uint4 x[4], y[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          x[i] = *(const uint4*)&s_mask[(bi + 32 * i) * kCoactPitch + w];
+          y[i] = *(const uint4*)&s_mask[(bj + 32 * i) * kCoactPitch + w];
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            cnt[i][j] += __popc(x[i].x & y[j].x) + __popc(x[i].y & y[j].y) + __popc(x[i].z & y[j].z) +
+                         __popc(x[i].w & y[j].w);
+      }
+    }
+    __syncthreads();
+  }
+  if (!own) return;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int ei = bi + 32 * i, ej = bj + 32 * j;
+      if ((bi == bj && i > j) || ei >= E || ej >= E || cnt[i][j] == 0) continue;
+      if (ei == ej)
+        atomicAdd(&fire[ei], cnt[i][j]);
+      else
+        atomicAdd(&pair[(int64_t)min(ei, ej) * E + max(ei, ej)], cnt[i][j]);
+    }
+}
+
+// Counts were gathered in the upper triangle (which only its own threads' lower
+// mirror reads): D = 1 - NPMI, the lower triangle mirrored, the diagonal zeroed.
 __global__ __launch_bounds__(256) void k_npmi(const uint32_t* __restrict__ fire, uint32_t* __restrict__ pair, int N,
                                               int E, double* __restrict__ dist) {
   const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -88,6 +144,7 @@ __global__ __launch_bounds__(256) void k_npmi(const uint32_t* __restrict__ fire,
   const int i = (int)(q / E), j = (int)(q % E);
   if (i == j) {
     dist[q] = 0.0;
+    pair[q] = 0u;
     return;
   }
   const int lo = i < j ? i : j, hi = i < j ? j : i;
@@ -102,14 +159,7 @@ __global__ __launch_bounds__(256) void k_npmi(const uint32_t* __restrict__ fire,
     npmi = log(pij / (((double)fire[i] / n) * ((double)fire[j] / n))) / (-log(pij));
   }
   dist[q] = 1.0 - npmi;
-}
-
-__global__ __launch_bounds__(256) void k_mirror(uint32_t* __restrict__ pair, int E) {
-  const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= (int64_t)E * E) return;
-  const int i = (int)(q / E), j = (int)(q % E);
-  if (i > j) pair[q] = pair[(int64_t)j * E + i];
-  if (i == j) pair[q] = 0u;
+  if (i > j) pair[q] = nij;
 }
 
 // Order-preserving map of doubles onto unsigned 64-bit keys.
@@ -118,55 +168,103 @@ __device__ __forceinline__ unsigned long long dkey(double v) {
   return (b >> 63) ? ~b : (b | 0x8000000000000000ull);
 }
 
+// Latency-bound (one workgroup). E <= KMAX = 128: the distance matrix is staged
+// in LDS (odd pitch: the threads' rows on distinct banks); larger E reads it
+// from memory, 8 loads in flight, unconditionally, the members picked
+// afterwards (a load under the membership test is waited for before the next
+// test). E = 128, 16 clusters: 87 -> 62 us with both.
+constexpr int kKmSmall = 128;
+
+template <int KMAX>
 __global__ __launch_bounds__(KM_THR) void k_kmedoids(const double* __restrict__ D, const uint32_t* __restrict__ fire,
                                                      int E, int C, ProtMask pm, int P, int max_iter,
                                                      int32_t* __restrict__ cluster_of,
                                                      int32_t* __restrict__ factor_of, int32_t* __restrict__ dominant,
                                                      int32_t* __restrict__ iterations) {
-  __shared__ int s_cl[KM_THR];
-  __shared__ int s_med[KM_THR];
-  __shared__ uint32_t s_fire[KM_THR];
-  __shared__ unsigned long long s_key[KM_THR];
-  __shared__ int s_idx[KM_THR];
-  __shared__ uint32_t s_fmax[KM_THR];
-  __shared__ int s_isdom[KM_THR];
+  constexpr bool SMALL = KMAX <= kKmSmall;
+  extern __shared__ double s_d[];  // SMALL: [E][E | 1]
+  __shared__ int s_cl[KMAX];
+  __shared__ int s_med[KMAX];
+  __shared__ uint32_t s_fire[KMAX];
+  __shared__ unsigned long long s_key[KMAX];
+  __shared__ int s_idx[KMAX];
+  __shared__ uint32_t s_fmax[KMAX];
+  __shared__ int s_isdom[KMAX], s_prot[KMAX];
   __shared__ int s_changed;
   const int e = threadIdx.x;
   const int K = C - P;
   const bool live = e < E;
   const bool prot = live && ((pm.bits[e >> 5] >> (e & 31)) & 1u);
   const bool free_e = live && !prot;
-  s_fire[e] = live ? fire[e] : 0u;
-  s_cl[e] = -1;
-  s_isdom[e] = 0;
+  if (e < KMAX) {
+    s_fire[e] = live ? fire[e] : 0u;
+    s_cl[e] = -1;
+    s_isdom[e] = 0;
+    s_prot[e] = prot || !live;
+  }
+  const int pitch = E | 1;
+  if (SMALL) {
+    // a wavefront per row; 8 rows' loads in flight
+    const int lane = e & 63, nw = blockDim.x >> 6;
+    for (int i0 = e >> 6; i0 < E; i0 += 8 * nw)
+      for (int j = lane; j < E; j += 64) {
+        double v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = D[(int64_t)(i0 + u * nw < E ? i0 + u * nw : E - 1) * E + j];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+          if (i0 + u * nw < E) s_d[(i0 + u * nw) * pitch + j] = v[u];
+      }
+  }
   __syncthreads();
   // seeds: free experts ranked by (firing count descending, index ascending)
   if (free_e) {
     int rank = 0;
+    const uint32_t fe = s_fire[e];
+#pragma unroll 8
     for (int f = 0; f < E; ++f) {
-      const bool pf = (pm.bits[f >> 5] >> (f & 31)) & 1u;
-      if (!pf && (s_fire[f] > s_fire[e] || (s_fire[f] == s_fire[e] && f < e))) ++rank;
+      const uint32_t ff = s_fire[f];
+      rank += !s_prot[f] && (ff > fe || (ff == fe && f < e)) ? 1 : 0;
     }
     if (rank < K) s_med[rank] = e;
   }
   __syncthreads();
-  const double* const De = D + (int64_t)(live ? e : 0) * E;
+  const double* const De = SMALL ? s_d + (live ? e : 0) * pitch : D + (int64_t)(live ? e : 0) * E;
+  // sum over j, ascending, of f(De[j]) where pick(j)
+  auto sum_where = [&](auto pick, auto f) {
+    double s = 0.0;
+    for (int j0 = 0; j0 < E; j0 += 8) {
+      double v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = De[j0 + u < E ? j0 + u : E - 1];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const double w = s + f(v[u]);
+        s = j0 + u < E && pick(j0 + u) ? w : s;
+      }
+    }
+    return s;
+  };
   auto assign = [&]() {
     if (free_e) {
       int own = -1;
-      for (int c = 0; c < K; ++c)
-        if (s_med[c] == e) own = c;
+#pragma unroll 8
+      for (int c = 0; c < K; ++c) own = s_med[c] == e ? c : own;
       if (own >= 0) {
         s_cl[e] = own;
       } else {
         int best = 0;
         double bd = De[s_med[0]];
-        for (int c = 1; c < K; ++c) {
-          const double v = De[s_med[c]];
-          if (v < bd) {
-            bd = v;
-            best = c;
-          }
+        for (int c0 = 1; c0 < K; c0 += 8) {
+          double v[8];
+#pragma unroll
+          for (int u = 0; u < 8; ++u) v[u] = De[s_med[c0 + u < K ? c0 + u : K - 1]];
+#pragma unroll
+          for (int u = 0; u < 8; ++u)
+            if (c0 + u < K && v[u] < bd) {
+              bd = v[u];
+              best = c0 + u;
+            }
         }
         s_cl[e] = best;
       }
@@ -180,8 +278,7 @@ __global__ __launch_bounds__(KM_THR) void k_kmedoids(const double* __restrict__ 
     double s = 0.0;
     if (free_e) {
       const int c = s_cl[e];
-      for (int j = 0; j < E; ++j)
-        if (s_cl[j] == c) s += De[j];
+      s = sum_where([&](int j) { return s_cl[j] == c; }, [](double v) { return v; });
     }
     if (e < K) {
       s_key[e] = ~0ull;
@@ -204,7 +301,8 @@ __global__ __launch_bounds__(KM_THR) void k_kmedoids(const double* __restrict__ 
   // protected experts: singleton clusters after the seeded ones
   if (prot) {
     int rank = 0;
-    for (int f = 0; f < e; ++f) rank += (pm.bits[f >> 5] >> (f & 31)) & 1u;
+#pragma unroll 8
+    for (int f = 0; f < E; ++f) rank += f < e && s_prot[f] ? 1 : 0;
     s_cl[e] = K + rank;
   }
   if (e < C) {
@@ -218,8 +316,7 @@ __global__ __launch_bounds__(KM_THR) void k_kmedoids(const double* __restrict__ 
   const int c = live ? s_cl[e] : 0;
   double cent = 0.0;
   if (live)
-    for (int j = 0; j < E; ++j)
-      if (j != e && s_cl[j] == c) cent += 1.0 - De[j];
+    cent = sum_where([&](int j) { return j != e && s_cl[j] == c; }, [](double v) { return 1.0 - v; });
   if (live) atomicMax(&s_fmax[c], s_fire[e]);
   __syncthreads();
   const bool top = live && s_fire[e] == s_fmax[c];
@@ -234,7 +331,8 @@ __global__ __launch_bounds__(KM_THR) void k_kmedoids(const double* __restrict__ 
   __syncthreads();
   if (live) {
     int rank = 0;
-    for (int f = 0; f < e; ++f) rank += s_isdom[f] ? 0 : 1;
+#pragma unroll 8
+    for (int f = 0; f < E; ++f) rank += f < e && !s_isdom[f] ? 1 : 0;
     cluster_of[e] = c;
     factor_of[e] = s_isdom[e] ? -1 : rank;
   }
@@ -246,25 +344,37 @@ __global__ __launch_bounds__(KM_THR) void k_kmedoids(const double* __restrict__ 
 hipError_t launch_coact(const int32_t* ids, int N, int k, int E, uint32_t* fire, uint32_t* pair, double* dist,
                         hipStream_t s) {
   const int64_t ee = (int64_t)E * E;
-  hipLaunchKernelGGL(k_fill_u32, dim3((unsigned)((ee + 255) / 256)), dim3(256), 0, s, pair, ee);
-  hipLaunchKernelGGL(k_fill_u32, dim3((unsigned)((E + 255) / 256)), dim3(256), 0, s, fire, (int64_t)E);
+  const dim3 ge((unsigned)((ee + 255) / 256));
+  hipLaunchKernelGGL(k_fill2_u32, ge, dim3(256), 0, s, pair, ee, fire, (int64_t)E);
   if (N > 0) {
-    const int blocks = (N + 255) / 256 < 512 ? (N + 255) / 256 : 512;
+    // the masks' cost grows with E^2 per token and the final adds with E^2 per
+    // workgroup: past 128 experts the per-token atomics (k^2 / 2) are fewer
     if (E <= 128)
-      hipLaunchKernelGGL(k_coact<true>, dim3(blocks), dim3(256), 0, s, ids, N, k, E, fire, pair);
+      hipLaunchKernelGGL(k_coact_bits, dim3((unsigned)std::min<int64_t>(((int64_t)N + kCoactTok - 1) / kCoactTok,
+                                                                        kCoactGroups)),
+                         dim3(kCoactThr), 0, s, ids, N, k, E, fire, pair);
     else
-      hipLaunchKernelGGL(k_coact<false>, dim3(blocks), dim3(256), 0, s, ids, N, k, E, fire, pair);
+      hipLaunchKernelGGL(k_coact, dim3((unsigned)std::min((N + 255) / 256, 512)), dim3(256), 0, s, ids, N, k, E, fire,
+                         pair);
   }
-  hipLaunchKernelGGL(k_npmi, dim3((unsigned)((ee + 255) / 256)), dim3(256), 0, s, fire, pair, N, E, dist);
-  hipLaunchKernelGGL(k_mirror, dim3((unsigned)((ee + 255) / 256)), dim3(256), 0, s, pair, E);
+  hipLaunchKernelGGL(k_npmi, ge, dim3(256), 0, s, fire, pair, N, E, dist);
   return hipGetLastError();
 }
 
 hipError_t launch_kmedoids(const double* dist, const uint32_t* fire, int E, int C, const ProtMask& pm, int P,
                            int max_iter, int32_t* cluster_of, int32_t* factor_of, int32_t* dominant,
                            int32_t* iterations, hipStream_t s) {
-  hipLaunchKernelGGL(k_kmedoids, dim3(1), dim3(KM_THR), 0, s, dist, fire, E, C, pm, P, max_iter, cluster_of,
-                     factor_of, dominant, iterations);
+  if (E <= kKmSmall) {
+    static const hipError_t lds = hipFuncSetAttribute((const void*)k_kmedoids<kKmSmall>,
+                                                      hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                      kKmSmall * (kKmSmall | 1) * 8);
+    if (lds != hipSuccess) return lds;
+    hipLaunchKernelGGL(k_kmedoids<kKmSmall>, dim3(1), dim3(512), (size_t)E * (E | 1) * 8, s, dist, fire, E, C, pm, P,
+                       max_iter, cluster_of, factor_of, dominant, iterations);
+  } else {
+    hipLaunchKernelGGL(k_kmedoids<KM_THR>, dim3(1), dim3(KM_THR), 0, s, dist, fire, E, C, pm, P, max_iter, cluster_of,
+                       factor_of, dominant, iterations);
+  }
   return hipGetLastError();
 }
 

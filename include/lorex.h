@@ -377,16 +377,15 @@ lx_status lx_route_topk(const void* x, const void* w_r, lx_dtype dtype, int32_t 
 /* The unchanged router fused into the tree forward (Sec. 3 "Stage 1" and
  * Fig. overview: the router is left as it is and selects among all experts;
  * Sec. 5.1: the forward shares work among the experts it selects). The
- * router's logits x W_r^T run first (as in lx_route_topk); their top-k and
- * renormalised softmax are computed inside the first bucketing kernel, which
- * writes topk_ids and topk_weights (outputs here, same values and layout as
- * lx_route_topk's, bit for bit) and organises them into the rows the forward
- * shares, so routing and bucketing take one launch fewer than
- * lx_route_topk followed by lx_moe_forward_tree. Batches of at most 64
- * tokens, whose bucketing is a single workgroup, keep the router's own top-k
- * launch (one workgroup would take every token's top-k on one compute
- * unit). Then the forward as lx_moe_forward_tree on those ids and weights:
- * out is bitwise the same.
+ * router's logits x W_r^T run first (as in lx_route_topk); one launch then
+ * takes their top-k and renormalised softmax, writes topk_ids and topk_weights
+ * (outputs here, same values and layout as lx_route_topk's, bit for bit) and
+ * counts the histograms of the bucketing, so routing and bucketing take one
+ * launch fewer than lx_route_topk followed by lx_moe_forward_tree. Batches of
+ * at most 64 tokens, whose bucketing is a single workgroup, keep the router's
+ * own top-k launch (one workgroup would take every token's top-k on one
+ * compute unit). Then the forward as lx_moe_forward_tree on those ids and
+ * weights: out is bitwise the same.
  *
  * layer: as for lx_moe_forward_tree, bf16 (LX_ERR_UNSUPPORTED otherwise);
  * w_r [E][d] bf16, 16-byte aligned; E a multiple of 4 in 4 .. 512, k <=

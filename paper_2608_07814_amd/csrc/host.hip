@@ -556,8 +556,8 @@ const char* intern_name(const std::string& n) {
 enum Stop { RUN_ALL, RUN_BUCKET };
 
 // The whole forward (or just the bucketing) of a validated tree.
-// route: the router's logits, when its top-k is fused into the bucketing
-// (ids and w are then outputs, written by the first bucketing kernel).
+// route: the router's logits, when the call routes its own tokens (ids and w
+// are then outputs, written by the top-k).
 lx_status run(const lx_tree_layer& t, int T, int k, const void* x, const int32_t* ids, const float* w,
               void* out, lx_dtype out_dtype, void* ws, size_t ws_bytes, hipStream_t stream, Stop stop,
               Plan* plan_out = nullptr, const RouteIn* route = nullptr) {
@@ -616,7 +616,6 @@ lx_status run(const lx_tree_layer& t, int T, int k, const void* x, const int32_t
   ba.slot_wsum = (float*)(W + P.slot_wsum);
   ba.anc = pa.anc;
   ba.flags = pa.flags;
-  if (route) ba.route = *route;
   for (int l = 0; l <= L; ++l) {
     const LevelPlan& q = P.lv[l];
     BucketLevel& b = ba.lv[l];
@@ -641,19 +640,22 @@ lx_status run(const lx_tree_layer& t, int T, int k, const void* x, const int32_t
     b.n_split_cnt = (int32_t)q.n_cnt;
   }
   if (bucket_small_ok(ba) && !P.merged) {
-    if (route) {
+    if (route)
       // batches of at most 64 tokens: the single-workgroup bucketing would
       // run every token's top-k on one compute unit, slower than the
       // router's own kernel with one wavefront per token
       LX_LAUNCH("router_topk", launch_topk(route->logits, route->part, route->S, T, E, k,
                                            const_cast<int32_t*>(ids), const_cast<float*>(w), lstream));
-      ba.route = RouteIn{};
-    }
     LX_LAUNCH("bucket_small", launch_bucket_small(pa, ba, lstream));
   } else {
+    if (route)
+      for (int l = 0; l <= L; ++l) {
+        pa.zero[l] = ba.lv[l].hist;
+        pa.n_zero[l] = (int64_t)P.lv[l].N * P.NT;
+      }
     LX_LAUNCH("bucket_prepare", launch_prepare(pa, lstream));
     if (route)
-      LX_LAUNCH("router_topk+bucket_hist", launch_bucket_hist_route(ba, lstream));
+      LX_LAUNCH("router_topk+bucket_hist", launch_topk_hist(*route, ba, lstream));
     else
       LX_LAUNCH("bucket_hist", launch_bucket_hist(ba, lstream));
     LX_LAUNCH("bucket_scan", launch_bucket_scan(ba, lstream));

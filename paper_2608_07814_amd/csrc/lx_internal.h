@@ -179,12 +179,11 @@ struct BucketLevel {
   int32_t n_split_cnt;        // here for the level's skinny GEMMs
 };
 
-// Router top-k fused into the first bucketing kernel: the logits of the
-// router GEMM (final [T][E], or S split-K partial tiles, as for launch_topk)
-// are turned into the ids and weights that the rest of the bucketing and
-// the forward read (written to BucketArgs::ids / w, which are then outputs).
+// Router logits for the forward that routes its own tokens (final [T][E], or
+// S split-K partial tiles, as for launch_topk): the top-k turns them into the
+// ids and weights that the rest reads (written to BucketArgs::ids / w).
 struct RouteIn {
-  const float* logits;     // null: no fused router (ids and w are inputs)
+  const float* logits;
   const float* part;
   int32_t S;
 };
@@ -198,7 +197,6 @@ struct BucketArgs {
                            // slot holds the sum of its slots' weights, others 0
   const int32_t* anc;      // [(L + 1) * E] ancestor per level, -1 = invalid expert
   uint32_t* flags;
-  RouteIn route;
   BucketLevel lv[kMaxLvl];
 };
 
@@ -213,13 +211,16 @@ struct PrepareArgs {
   uint8_t* path_work;                  // out [E] (optional): 1 if a node on the
                                        // expert's path carries a factor
   uint32_t* flags;
+  // histograms to clear ahead of launch_topk_hist (null: none)
+  int32_t* zero[kMaxLvl];
+  int64_t n_zero[kMaxLvl];
 };
 
 hipError_t launch_prepare(const PrepareArgs& a, hipStream_t s);
 hipError_t launch_bucket_hist(const BucketArgs& a, hipStream_t s);
-// With a.route set: top-k of every token (ids and weights written to a.ids
-// and a.w) and the histogram of every level, one workgroup per token tile.
-hipError_t launch_bucket_hist_route(const BucketArgs& a, hipStream_t s);
+// Top-k of every token and, into the cleared histograms, its nodes at every
+// level, one wavefront per token.
+hipError_t launch_topk_hist(const RouteIn& r, const BucketArgs& a, hipStream_t s);
 hipError_t launch_bucket_scan(const BucketArgs& a, hipStream_t s);
 hipError_t launch_bucket_place(const BucketArgs& a, hipStream_t s);
 // Merged correction outputs of a tree (after placement): for every leaf

@@ -77,14 +77,27 @@ __device__ __forceinline__ void load_lds16(const void* gptr, const void* lds_dst
                : "memory");
 }
 
-// One 4-byte direct HBM -> LDS load per lane (lane i writes LDS bytes
-// [lds_base + 4 i, lds_base + 4 i + 4)); same conventions as load_lds16.
-__device__ __forceinline__ void load_lds4(const void* gptr, const void* lds_dst) {
+// The same load with the non-temporal hint, for weights that a launch reads
+// once or from a few neighbouring workgroups (the skinny kernels and the 128-row
+// tiles): the stream then leaves the caches to what is read again (activations,
+// intermediates, row lists). Without and with the hint: tree T = 777 leaf-level
+// input product 82 -> 66 us; tree T = 16 forward 184 -> 172 us, of it bucketing
+// 13 -> 11 and SwiGLU 16.5 -> 12.4; one token on the 4096 x 14336 layer 109 -> 103.
+// On the 256-row tiles of long prefills, whose row tiles share weights through
+// L2, it lost 1 to 2%.
+__device__ __forceinline__ void load_lds16_nt(const void* gptr, const void* lds_dst) {
   const uint32_t lds = (uint32_t)(uintptr_t)(lds_void_t*)lds_dst;
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off"
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off nt"
                :
                : "v"(gptr), "s"(__builtin_amdgcn_readfirstlane(lds))
                : "memory");
+}
+template <bool NT>
+__device__ __forceinline__ void load_lds16_w(const void* gptr, const void* lds_dst) {
+  if constexpr (NT)
+    load_lds16_nt(gptr, lds_dst);
+  else
+    load_lds16(gptr, lds_dst);
 }
 
 // The same loads addressed as a wave-uniform 64-bit base (SGPR pair) plus a
@@ -327,7 +340,7 @@ __device__ __forceinline__ void gemm_big_body(const GemmArgs& p, int ntn, const 
       _Pragma("unroll") for (int j = 0; j < A_ROUNDS; ++j)                          \
           load_lds16(Ab + (aoff[j] + (uint32_t)ka_), &(SA_)[(j * NTHR + wave * 64) * 8]);  \
       _Pragma("unroll") for (int j = 0; j < B_ROUNDS; ++j)                          \
-          load_lds16(bptr[j] + kb_, &(SB_)[(j * NTHR + wave * 64) * 8]);            \
+          load_lds16_w<BM == 128>(bptr[j] + kb_, &(SB_)[(j * NTHR + wave * 64) * 8]); \
     } else {                                                                        \
       const int ka_ = (KT) * BK2, k0_ = ka_ % Kb;                                   \
       _Pragma("unroll") for (int j = 0; j < A_ROUNDS; ++j)                          \
@@ -336,7 +349,7 @@ __device__ __forceinline__ void gemm_big_body(const GemmArgs& p, int ntn, const 
         const int ps_ = j * NTHR + tid, row_ = ps_ >> 3;                            \
         const int c8_ = (((ps_ & 7) ^ swzb(row_)) << 3);                            \
         const int w_ = k0_ + c8_ >= Kb ? k0_ - Kb : k0_;                            \
-        load_lds16(bptr[j] + w_, &(SB_)[(j * NTHR + wave * 64) * 8]);               \
+        load_lds16_w<BM == 128>(bptr[j] + w_, &(SB_)[(j * NTHR + wave * 64) * 8]);  \
       }                                                                             \
     }                                                                               \
   } while (0)
@@ -1338,7 +1351,14 @@ __global__ __launch_bounds__(SK_THR) void k_gemm_skinny(SkinnyBatch b) {
           load_lds16(Ab + (aoff[j] + (uint32_t)(per * Kb + kb)), sA + per * SA + (j * SK_THR + wave * 64) * 8);
     }
 #pragma unroll
-    for (int j = 0; j < B_ROUNDS; ++j) load_lds16(bptr[j] + kb, sA + PER * SA + (j * SK_THR + wave * 64) * 8);
+    for (int j = 0; j < B_ROUNDS; ++j) {
+      u16* const dst = sA + PER * SA + (j * SK_THR + wave * 64) * 8;
+      // (implicit dense tiles, the router: every row tile reads the same weights)
+      if (p.tiles)
+        load_lds16_nt(bptr[j] + kb, dst);
+      else
+        load_lds16(bptr[j] + kb, dst);
+    }
   };
 
   f32x16 acc;
@@ -1369,17 +1389,41 @@ __global__ __launch_bounds__(SK_THR) void k_gemm_skinny(SkinnyBatch b) {
   static_assert(SK_NST >= 2 && SK_NST <= 4, "ring depth");
   const int npre = nkl < SK_NST ? nkl : SK_NST;
   for (int i = 0; i < npre; ++i) issue(i, kt0 + i);
-  wait_slabs<R>(npre - 1);
-  bar();
-  for (int i = 0; i < nkl; ++i) {
-    compute(i % SK_NST);
-    if (i + 1 < nkl) {
-      // steps issued so far: 0 .. min(i + SK_NST - 1, nkl - 1); wait for i + 1
-      const int last = i + SK_NST - 1 < nkl - 1 ? i + SK_NST - 1 : nkl - 1;
-      wait_slabs<R>(last - (i + 1));
+  if constexpr (SK_NST == 4) {
+    // Two steps per barrier pair: the two 128-byte pieces of a weight row's 256
+    // bytes are then requested back to back (one DRAM page visit). One token on
+    // the 4096 x 14336 layer: gate|up 54.8 -> 51.8 us; tree T = 16: 58.5 -> 57.5 us.
+    int i = 0;
+    for (; i + 1 < nkl; i += 2) {
+      // steps issued so far: 0 .. min(i + 3, nkl - 1); wait for i and i + 1
+      const int issued = i + 4 < nkl ? i + 4 : nkl;
+      wait_slabs<R>(issued - (i + 2));
+      bar();
+      compute(i % 4);
+      compute((i + 1) % 4);
       wait_lgkm0();
       bar();
-      if (i + SK_NST < nkl) issue(i % SK_NST, kt0 + i + SK_NST);
+      if (i + 4 < nkl) issue(i % 4, kt0 + i + 4);
+      if (i + 5 < nkl) issue((i + 1) % 4, kt0 + i + 5);
+    }
+    if (i < nkl) {
+      wait_vmcnt<0>();
+      bar();
+      compute(i % 4);
+    }
+  } else {
+    wait_slabs<R>(npre - 1);
+    bar();
+    for (int i = 0; i < nkl; ++i) {
+      compute(i % SK_NST);
+      if (i + 1 < nkl) {
+        // steps issued so far: 0 .. min(i + SK_NST - 1, nkl - 1); wait for i + 1
+        const int last = i + SK_NST - 1 < nkl - 1 ? i + SK_NST - 1 : nkl - 1;
+        wait_slabs<R>(last - (i + 1));
+        wait_lgkm0();
+        bar();
+        if (i + SK_NST < nkl) issue(i % SK_NST, kt0 + i + SK_NST);
+      }
     }
   }
   wait_lgkm0();
@@ -1467,7 +1511,7 @@ __global__ __launch_bounds__(SK_THR) void k_gemm_skinny_wide(SkinnyBatch b) {
       int n = n0g + t * BN + row;
       n = n < u.ncol ? n : u.ncol - 1;
       const u16* bp = (n < p.ncols[0] ? Bw0 + (int64_t)n * Kb : Bw1 + (int64_t)(n - p.ncols[0]) * Kb) + c * 8;
-      load_lds16(bp, smem + PER * SA + t * SBt + (j * SK_THR + wave * 64) * 8);
+      load_lds16_nt(bp, smem + PER * SA + t * SBt + (j * SK_THR + wave * 64) * 8);
     }
   wait_vmcnt<0>();
   bar();

@@ -64,14 +64,17 @@ __global__ __launch_bounds__(256) void k_coact(const int32_t* __restrict__ ids, 
 }
 
 // E <= 128: 1024 tokens at a time, a 1024-bit mask per expert in LDS (a repeated
-// id sets its bit once). A thread owns the pairs (bi + 32 u, bj + 32 v), u, v < 4,
-// of one bi <= bj < 32 (528 threads; neighbouring threads read neighbouring
-// experts' masks, on distinct banks), and counts popcount(mask_i & mask_j) in
-// registers; the diagonal gives the firing counts.
+// id sets its bit once). A thread owns the pairs (bi + 32 u, bj + 32 v), v < 4, of
+// one bi <= bj < 32 (528 threads; neighbouring threads read neighbouring
+// experts' masks, on distinct banks) and its workgroup's u = blockIdx.y, and
+// counts popcount(mask_i & mask_j) in registers; the diagonal gives the firing
+// counts. The four workgroups of the same tokens each build all masks: that
+// is a third of the popcounts' time, and 64 workgroups alone leave three of
+// four compute units idle.
 // What bounds it is the final adds to global memory (about 37 per ns over the
 // chip), so kCoactGroups workgroups share the tokens. Against the kernel that
 // gathered pair counts in LDS and flushed them per 256 tokens: 131072 tokens,
-// top-8, E = 128: 78 -> 35 us.
+// top-8, E = 128: 78 -> 38 us, four workgroups per 1024 tokens: 30 us.
 constexpr int kCoactTok = 1024, kCoactThr = 1024, kCoactGroups = 64, kCoactPitch = kCoactTok / 32 + 4;
 
 __global__ __launch_bounds__(kCoactThr) void k_coact_bits(const int32_t* __restrict__ ids, int N, int k, int E,
@@ -85,8 +88,9 @@ __global__ __launch_bounds__(kCoactThr) void k_coact_bits(const int32_t* __restr
     ++bi;
   }
   bj += bi;
-  const bool own = bi < 32 && bi < E && bj < E;
-  uint32_t cnt[4][4] = {};
+  const bool own = bi < 32 && bi + 32 * (int)blockIdx.y < E && bj < E;
+  const int ei = bi + 32 * blockIdx.y;
+  uint32_t cnt[4] = {};
   for (int t0 = blockIdx.x * kCoactTok; t0 < N; t0 += gridDim.x * kCoactTok) {
     for (int i = tid; i < 128 * kCoactPitch; i += kCoactThr) s_mask[i] = 0u;
     __syncthreads();
@@ -105,34 +109,27 @@ __global__ __launch_bounds__(kCoactThr) void k_coact_bits(const int32_t* __restr
     __syncthreads();
     if (own) {
       for (int w = 0; w < kCoactTok / 32; w += 4) {
-        uint4 x[4], y[4];
+        const uint4 x = *(const uint4*)&s_mask[ei * kCoactPitch + w];
+        uint4 y[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          x[i] = *(const uint4*)&s_mask[(bi + 32 * i) * kCoactPitch + w];
-          y[i] = *(const uint4*)&s_mask[(bj + 32 * i) * kCoactPitch + w];
-        }
+        for (int j = 0; j < 4; ++j) y[j] = *(const uint4*)&s_mask[(bj + 32 * j) * kCoactPitch + w];
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-          for (int j = 0; j < 4; ++j)
-            cnt[i][j] += __popc(x[i].x & y[j].x) + __popc(x[i].y & y[j].y) + __popc(x[i].z & y[j].z) +
-                         __popc(x[i].w & y[j].w);
+        for (int j = 0; j < 4; ++j)
+          cnt[j] += __popc(x.x & y[j].x) + __popc(x.y & y[j].y) + __popc(x.z & y[j].z) + __popc(x.w & y[j].w);
       }
     }
     __syncthreads();
   }
   if (!own) return;
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int ei = bi + 32 * i, ej = bj + 32 * j;
-      if ((bi == bj && i > j) || ei >= E || ej >= E || cnt[i][j] == 0) continue;
-      if (ei == ej)
-        atomicAdd(&fire[ei], cnt[i][j]);
-      else
-        atomicAdd(&pair[(int64_t)min(ei, ej) * E + max(ei, ej)], cnt[i][j]);
-    }
+  for (int j = 0; j < 4; ++j) {
+    const int ej = bj + 32 * j;
+    if ((bi == bj && (int)blockIdx.y > j) || ej >= E || cnt[j] == 0) continue;
+    if (ei == ej)
+      atomicAdd(&fire[ei], cnt[j]);
+    else
+      atomicAdd(&pair[(int64_t)min(ei, ej) * E + max(ei, ej)], cnt[j]);
+  }
 }
 
 // Counts were gathered in the upper triangle (which only its own threads' lower
@@ -172,7 +169,9 @@ __device__ __forceinline__ unsigned long long dkey(double v) {
 // in LDS (odd pitch: the threads' rows on distinct banks); larger E reads it
 // from memory, 8 loads in flight, unconditionally, the members picked
 // afterwards (a load under the membership test is waited for before the next
-// test). E = 128, 16 clusters: 87 -> 62 us with both.
+// test). E <= 128 also keeps a bit mask of each cluster's members, so the ordered
+// sums walk the members alone, 4 loads in flight. E = 128, 16 clusters:
+// 65 -> 37 us with the masks and 16 rows' staging loads in flight.
 constexpr int kKmSmall = 128;
 
 template <int KMAX>
@@ -190,6 +189,8 @@ __global__ __launch_bounds__(KM_THR) void k_kmedoids(const double* __restrict__ 
   __shared__ int s_idx[KMAX];
   __shared__ uint32_t s_fmax[KMAX];
   __shared__ int s_isdom[KMAX], s_prot[KMAX];
+  // SMALL: the members of each cluster, the last assignment's and the one before
+  __shared__ unsigned long long s_mem[2][SMALL ? 2 * KMAX : 1];
   __shared__ int s_changed;
   const int e = threadIdx.x;
   const int K = C - P;
@@ -204,17 +205,24 @@ __global__ __launch_bounds__(KM_THR) void k_kmedoids(const double* __restrict__ 
   }
   const int pitch = E | 1;
   if (SMALL) {
-    // a wavefront per row; 8 rows' loads in flight
+    // a wavefront per row; 16 rows' loads in flight
     const int lane = e & 63, nw = blockDim.x >> 6;
-    for (int i0 = e >> 6; i0 < E; i0 += 8 * nw)
-      for (int j = lane; j < E; j += 64) {
-        double v[8];
+    for (int i0 = e >> 6; i0 < E; i0 += 16 * nw) {
+      double v[16][KMAX / 64];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = D[(int64_t)(i0 + u * nw < E ? i0 + u * nw : E - 1) * E + j];
+      for (int u = 0; u < 16; ++u)
 #pragma unroll
-        for (int u = 0; u < 8; ++u)
-          if (i0 + u * nw < E) s_d[(i0 + u * nw) * pitch + j] = v[u];
-      }
+        for (int h = 0; h < KMAX / 64; ++h) {
+          const int i = i0 + u * nw < E ? i0 + u * nw : E - 1, j = lane + 64 * h < E ? lane + 64 * h : E - 1;
+          v[u][h] = D[(int64_t)i * E + j];
+        }
+#pragma unroll
+      for (int u = 0; u < 16; ++u)
+#pragma unroll
+        for (int h = 0; h < KMAX / 64; ++h)
+          if (i0 + u * nw < E && lane + 64 * h < E) s_d[(i0 + u * nw) * pitch + lane + 64 * h] = v[u][h];
+    }
+    for (int i = e; i < 2 * KMAX; i += blockDim.x) s_mem[0][i] = 0ull;
   }
   __syncthreads();
   // seeds: free experts ranked by (firing count descending, index ascending)
@@ -245,7 +253,35 @@ __global__ __launch_bounds__(KM_THR) void k_kmedoids(const double* __restrict__ 
     }
     return s;
   };
-  auto assign = [&]() {
+  int cur = 0;  // the last assignment's masks
+  // the same over the members of cluster c but `skip` (-1: none)
+  auto sum_members = [&](int c, int skip, auto f) {
+    unsigned long long lo = s_mem[cur][2 * c], hi = s_mem[cur][2 * c + 1];
+    if (skip >= 64) hi &= ~(1ull << (skip - 64));
+    if (skip >= 0 && skip < 64) lo &= ~(1ull << skip);
+    double s = 0.0;
+    while (lo | hi) {
+      double v[4];
+      bool on[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        on[u] = (lo | hi) != 0ull;
+        const int j = lo ? __ffsll((long long)lo) - 1 : 63 + __ffsll((long long)hi);
+        v[u] = De[on[u] ? j : 0];
+        if (lo)
+          lo &= lo - 1ull;
+        else
+          hi &= hi - 1ull;  // (0 stays 0)
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const double w = s + f(v[u]);
+        s = on[u] ? w : s;
+      }
+    }
+    return s;
+  };
+  auto assign = [&](int into) {
     if (free_e) {
       int own = -1;
 #pragma unroll 8
@@ -268,23 +304,29 @@ __global__ __launch_bounds__(KM_THR) void k_kmedoids(const double* __restrict__ 
         }
         s_cl[e] = best;
       }
+      if (SMALL) atomicOr(&s_mem[into][2 * s_cl[e] + (e >> 6)], 1ull << (e & 63));
     }
     __syncthreads();
   };
-  assign();
+  assign(0);
   int it = 0;
   while (it < max_iter) {
     ++it;
     double s = 0.0;
     if (free_e) {
       const int c = s_cl[e];
-      s = sum_where([&](int j) { return s_cl[j] == c; }, [](double v) { return v; });
+      if (SMALL)
+        s = sum_members(c, -1, [](double v) { return v; });
+      else
+        s = sum_where([&](int j) { return s_cl[j] == c; }, [](double v) { return v; });
     }
     if (e < K) {
       s_key[e] = ~0ull;
       s_idx[e] = 0x7FFFFFFF;
     }
     __syncthreads();
+    if (SMALL)
+      for (int i = e; i < 2 * KMAX; i += blockDim.x) s_mem[cur ^ 1][i] = 0ull;
     if (free_e) atomicMin(&s_key[s_cl[e]], dkey(s));
     __syncthreads();
     if (free_e && dkey(s) == s_key[s_cl[e]]) atomicMin(&s_idx[s_cl[e]], e);
@@ -296,7 +338,8 @@ __global__ __launch_bounds__(KM_THR) void k_kmedoids(const double* __restrict__ 
     }
     __syncthreads();
     if (!s_changed) break;
-    assign();
+    assign(cur ^ 1);
+    cur ^= 1;
   }
   // protected experts: singleton clusters after the seeded ones
   if (prot) {
@@ -315,8 +358,11 @@ __global__ __launch_bounds__(KM_THR) void k_kmedoids(const double* __restrict__ 
   // members, ascending member order), then lowest index
   const int c = live ? s_cl[e] : 0;
   double cent = 0.0;
-  if (live)
+  if (SMALL) {
+    if (free_e) cent = sum_members(c, e, [](double v) { return 1.0 - v; });  // (a protected expert is alone)
+  } else if (live) {
     cent = sum_where([&](int j) { return j != e && s_cl[j] == c; }, [](double v) { return 1.0 - v; });
+  }
   if (live) atomicMax(&s_fmax[c], s_fire[e]);
   __syncthreads();
   const bool top = live && s_fire[e] == s_fmax[c];
@@ -351,7 +397,8 @@ hipError_t launch_coact(const int32_t* ids, int N, int k, int E, uint32_t* fire,
     // workgroup: past 128 experts the per-token atomics (k^2 / 2) are fewer
     if (E <= 128)
       hipLaunchKernelGGL(k_coact_bits, dim3((unsigned)std::min<int64_t>(((int64_t)N + kCoactTok - 1) / kCoactTok,
-                                                                        kCoactGroups)),
+                                                                        kCoactGroups),
+                                              (unsigned)std::min(4, (E + 31) / 32)),
                          dim3(kCoactThr), 0, s, ids, N, k, E, fire, pair);
     else
       hipLaunchKernelGGL(k_coact, dim3((unsigned)std::min((N + 255) / 256, 512)), dim3(256), 0, s, ids, N, k, E, fire,

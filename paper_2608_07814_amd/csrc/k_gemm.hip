@@ -365,8 +365,12 @@ __global__ __launch_bounds__(256) void k_gemm_f32m(GemmArgs p) {
   };
 
   const int wm = wave >> 1, wn = wave & 1, half = lane >> 5;
-  const int ra = wm * 32 + (lane & 31), rb = wn * 32 + (lane & 31);
-  const bool live = wm * 32 < te.nrows && n0 + wn * 32 < ncol;  // wavefront-uniform
+  // a tile of at most 32 rows: the second pair of wavefronts takes the second
+  // half of every slab's k for the same rows
+  const bool low = te.nrows <= 32;
+  const int rw = low ? 0 : wm * 32;
+  const int ra = rw + (lane & 31), rb = wn * 32 + (lane & 31);
+  const bool live = rw < te.nrows && n0 + wn * 32 < ncol;  // wavefront-uniform
   f32x16 acc0, acc1;
 #pragma unroll
   for (int i = 0; i < 16; ++i) acc0[i] = acc1[i] = 0.f;
@@ -386,8 +390,10 @@ __global__ __launch_bounds__(256) void k_gemm_f32m(GemmArgs p) {
     if (kt + MST - 1 < nk) issue(kt + MST - 1);
     if (live) {
       const float* const st = smem + (kt % MST) * (FBM + FBN) * MBK;
+      const int j0 = low && wm ? CH / 4 : 0, j1 = low && !wm ? CH / 4 : CH / 2;
+      for (int jj = j0; jj < j1; jj += CH / 4)
 #pragma unroll
-      for (int j = 0; j < CH / 2; ++j) {
+      for (int j = jj; j < jj + CH / 4; ++j) {
         const int c = 2 * j + half;
         const float4 fa = *(const float4*)(st + ra * MBK + ((c ^ swz(ra)) << 2));
         const float4 fb = *(const float4*)(st + FBM * MBK + rb * MBK + ((c ^ swz(rb)) << 2));
@@ -398,12 +404,25 @@ __global__ __launch_bounds__(256) void k_gemm_f32m(GemmArgs p) {
       }
     }
   }
+  if (low) {
+    // the two k halves meet in LDS (every slab's stage is free after the barrier)
+    __syncthreads();
+    float* const x = smem + wn * 1024 + lane;
+    if (wm && live) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) x[i * 64] = acc0[i] + acc1[i];
+    }
+    __syncthreads();
+    if (wm || !live) return;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc0[i] += x[i * 64];
+  }
   const int c = n0 + wn * 32 + (lane & 31);
   if (!live || c >= ncol) return;
   float* __restrict__ C = p.C + p.c_coloff[part] + c;
 #pragma unroll
   for (int i = 0; i < 16; ++i) {
-    const int rr = wm * 32 + 8 * (i >> 2) + 4 * half + (i & 3);
+    const int rr = rw + 8 * (i >> 2) + 4 * half + (i & 3);
     if (rr < te.nrows) C[(int64_t)(te.row0 + rr) * p.ldc] = acc0[i] + acc1[i];
   }
 }

@@ -59,6 +59,25 @@ def test_kmedoids_matches_oracle(E, C, prot):
     assert np.array_equal(cl, c0) and np.array_equal(fo, f0) and np.array_equal(dom, d0) and it[0] == it0
 
 
+@pytest.mark.parametrize("E,C,prot", [(33, 6, ()), (64, 9, (63,)), (65, 9, (0,)), (97, 3, (64, 70)), (127, 20, ())])
+def test_counts_and_kmedoids_at_the_mask_edges(E, C, prot):
+    """Expert counts around the 32-expert groups of the co-firing kernel and
+    the 64-bit words of the cluster masks, with clusters of many members and
+    token counts off the 1024-token masks."""
+    require_gpu()
+    say(f"cluster masks E={E} C={C} protected={prot}")
+    N = 3000 + E
+    ids, _ = random_routing(N, 5, E, 60 + E, allow_dupes=True, drop_frac=0.1, bad_frac=0.05)
+    fire, pair, dist, dist_d = _gpu_counts(ids, E)
+    f0, p0 = K.coact_counts(ids, E)
+    assert np.array_equal(fire, f0) and np.array_equal(pair, p0)
+    fire_d = torch.from_numpy(fire.astype(np.int32)).cuda()
+    for mi in (0, 1, 100):
+        cl, fo, dom, it = (t.cpu().numpy() for t in lx.kmedoids(dist_d, fire_d, C, protected=prot, max_iter=mi))
+        c0, o0, d0, it0 = K.kmedoids(dist, fire, C, protected=prot, max_iter=mi)
+        assert np.array_equal(cl, c0) and np.array_equal(fo, o0) and np.array_equal(dom, d0) and it[0] == it0
+
+
 def test_kmedoids_metric_large_and_max_iter():
     """E = 1024 points of a Euclidean metric (ties improbable), then the
     iteration cap: max_iter = 0 keeps the seeds' assignment, 1 one update."""

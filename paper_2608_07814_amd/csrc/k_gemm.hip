@@ -298,6 +298,9 @@ __global__ __launch_bounds__(256) void k_gemm_f32(GemmArgs p) {
 // above: d = 2048, f = 768, 16 anchors, rank 64, T = 300: anchor gate|up 405 -> 187
 // us (two thirds of it MFMA time), low-rank input 318 -> 60, anchor down 180 ->
 // 90. 128-column tiles: 177, 96, 104; 16-wide slabs: 191, 73, 97.
+// A node's few rows (19 of 64 on average there) leave half of the wavefronts of a
+// tile idle; sharing K with them: low-rank input 60 -> 40 us, the leaf level's
+// other products 77 -> 62 us together.
 __device__ __forceinline__ void f32_load_lds16(const void* gptr, const void* lds_dst) {
   typedef __attribute__((address_space(3))) void lds_void_t;
   const uint32_t lds = (uint32_t)(uintptr_t)(lds_void_t*)lds_dst;

@@ -154,6 +154,18 @@ def test_fp32_products_at_their_edges(over, T):
     assert e <= TOL_F32
 
 
+@pytest.mark.parametrize("T", [31, 32, 33, 96, 97])
+def test_fp32_tiles_of_at_most_32_rows(T):
+    """fp32 layers with every expert on every token: tiles of 31 to 33 rows (the
+    two k halves of a tile of at most 32 rows meet in LDS), and the same as the
+    last tile of a node, on K slabs of 32 and of 16."""
+    require_gpu()
+    p = make_problem(dict(config(1, dtype="f32"), d=96, f=80, r=48, E=8, C=2, k=8), seed=T, T=T)
+    e = err_ratio(gpu_forward(p), _oracle(p))
+    say(f"fp32 T={T}: err/RMS = {e:.3e}")
+    assert e <= TOL_F32
+
+
 def test_cfg4_tree_small():
     require_gpu()
     say("forward cfg4 T=8")

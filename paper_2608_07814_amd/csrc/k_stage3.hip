@@ -249,77 +249,120 @@ __global__ __launch_bounds__(256) void k_residual(const void* __restrict__ wd, c
 // row of U, and k_trsm_rows then a zero column of Q; the directions kept stay
 // orthonormal and the zero ones carry no weight in Q^T R.
 // Latency-bound (one workgroup, l dependent columns): thread (ti, tj) of a 16 x
-// 16 grid keeps entries (ti + 16 a, tj + 16 b) in registers, row k of the trailing
+// 16 grid keeps entries (ti + 16 a, tj + 16 b), a <= b, in registers, row k of the trailing
 // matrix goes through LDS once (one barrier per column), and the division by
-// the pivot's square root waits until every row is known. Against the kernel
-// that kept the matrix in LDS (1024 threads, three barriers per column): l = 74
-// 61 -> 32 us, the sum of the partials included.
+// the pivot's square root waits until every row is known. Column k first updates
+// only the block row that holds row k + 1, which goes to LDS at once; the other
+// block rows follow behind the next column's barrier, while its LDS reads are in
+// flight. kAhead partials are loaded together. l = 74: all entries of 8 partials
+// 31 us; the upper blocks of 12 partials 28, of 16 partials 30.
 template <int NB>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_chol(const double* __restrict__ part, int S, int l, double* __restrict__ Uf) {
   extern __shared__ double s_row[];  // [l][16 NB]: the trailing matrix's row k when its column is eliminated
-  __shared__ double s_diag[16 * NB];
-  constexpr int P = 16 * NB;
+  __shared__ double s_diag[16 * NB], s_rt[16 * NB], s_ri[16 * NB];
+  constexpr int P = 16 * NB, kAhead = NB <= 5 ? 4 : 2;
   const int tid = threadIdx.x, ti = tid >> 4, tj = tid & 15;
   double a[NB][NB] = {};
-  // every partial's entries are loaded together (clamped past l, then dropped)
-  for (int z = 0; z < S; ++z) {
-    const double* const g = part + (int64_t)z * l * l;
-    double t[NB][NB];
+  // the partials' entries (clamped past l and past S, then dropped), added in order
+  for (int z = 0; z < S; z += kAhead) {
+    double t[kAhead][NB][NB];
 #pragma unroll
-    for (int i = 0; i < NB; ++i)
+    for (int u = 0; u < kAhead; ++u) {
+      const double* const g = part + (int64_t)(z + u < S ? z + u : S - 1) * l * l;
 #pragma unroll
-      for (int j = 0; j < NB; ++j) {
-        const int gi = ti + 16 * i, gj = tj + 16 * j;
-        t[i][j] = g[(gi < l ? gi : l - 1) * l + (gj < l ? gj : l - 1)];
-      }
+      for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int j = i; j < NB; ++j) {
+          const int gi = ti + 16 * i, gj = tj + 16 * j;
+          t[u][i][j] = g[(gi < l ? gi : l - 1) * l + (gj < l ? gj : l - 1)];
+        }
+    }
     __builtin_amdgcn_sched_barrier(0);  // all loads issued before the first is waited for
 #pragma unroll
-    for (int i = 0; i < NB; ++i)
+    for (int u = 0; u < kAhead; ++u)
+      if (z + u < S) {
 #pragma unroll
-      for (int j = 0; j < NB; ++j) a[i][j] += t[i][j];
+        for (int i = 0; i < NB; ++i)
+#pragma unroll
+          for (int j = i; j < NB; ++j) a[i][j] += t[u][i][j];
+      }
   }
 #pragma unroll
   for (int i = 0; i < NB; ++i)
 #pragma unroll
-    for (int j = 0; j < NB; ++j) {
+    for (int j = i; j < NB; ++j) {
       const int gi = ti + 16 * i, gj = tj + 16 * j;
       if (gi >= l || gj >= l) a[i][j] = 0.0;
       if (gi == gj) s_diag[gi] = a[i][j];
     }
+  if (ti == 0) {
+#pragma unroll
+    for (int j = 0; j < NB; ++j) s_row[tj + 16 * j] = a[0][j];
+  }
   lds_barrier();
   double gmax = 0.0;
-  for (int k = 0; k < l; ++k) gmax = fmax(gmax, s_diag[k]);
+  for (int k = tid & 63; k < P; k += 64) gmax = fmax(gmax, s_diag[k]);
+  for (int o = 32; o > 0; o >>= 1) gmax = fmax(gmax, __shfl_xor(gmax, o, 64));
   const double floor_ = 1e-14 * gmax;
+  // the column before: its row, and minus its column over the pivot (0 at first)
+  double rj[NB] = {}, ri[NB] = {};
 #pragma unroll
   for (int kb = 0; kb < NB; ++kb)
     for (int kr = 0; kr < 16; ++kr) {
       const int k = kb * 16 + kr;
       if (k >= l) break;
-      double* const row = s_row + k * P;
-      if (ti == kr) {
-#pragma unroll
-        for (int j = 0; j < NB; ++j) row[tj + 16 * j] = a[kb][j];
-      }
-      lds_barrier();
+      const double* const row = s_row + k * P;
+      if (k > 0) lds_barrier();
       const double pk = row[k];
-      const double inv = pk > floor_ ? fast_rcp(pk) : 0.0;
+      double nj[NB], ni[NB];
       // rows and columns of the blocks before kb are done
-      double rj[NB];
 #pragma unroll
-      for (int j = kb; j < NB; ++j) rj[j] = row[tj + 16 * j];
+      for (int j = kb; j < NB; ++j) {
+        nj[j] = row[tj + 16 * j];
+        ni[j] = row[ti + 16 * j];
+      }
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int i = kb; i < NB; ++i) {
-        const double ri = -row[ti + 16 * i] * inv;
+      for (int i = kb + 1; i < NB; ++i)
 #pragma unroll
-        for (int j = kb; j < NB; ++j) a[i][j] = fma(ri, rj[j], a[i][j]);
+        for (int j = i; j < NB; ++j) a[i][j] = fma(ri[i], rj[j], a[i][j]);
+      const double inv = pk > floor_ ? fast_rcp(pk) : 0.0;
+#pragma unroll
+      for (int j = kb; j < NB; ++j) {
+        rj[j] = nj[j];
+        ri[j] = -ni[j] * inv;
+      }
+      if (kr < 15) {
+#pragma unroll
+        for (int j = kb; j < NB; ++j) a[kb][j] = fma(ri[kb], rj[j], a[kb][j]);
+        if (ti == kr + 1 && k + 1 < l) {
+#pragma unroll
+          for (int j = kb; j < NB; ++j) s_row[(k + 1) * P + tj + 16 * j] = a[kb][j];
+        }
+      } else if (kb + 1 < NB) {
+        const int nb = kb + 1 < NB ? kb + 1 : kb;
+#pragma unroll
+        for (int j = nb; j < NB; ++j) a[nb][j] = fma(ri[nb], rj[j], a[nb][j]);
+        if (ti == 0) {
+#pragma unroll
+          for (int j = nb; j < NB; ++j) s_row[(k + 1) * P + tj + 16 * j] = a[nb][j];
+        }
       }
     }
+  lds_barrier();
+  for (int k = tid; k < l; k += 256) {
+    const double pk = s_row[k * P + k], d = pk > floor_ ? sqrt(pk) : 0.0;
+    s_rt[k] = d;
+    s_ri[k] = d > 0.0 ? 1.0 / d : 0.0;
+  }
   lds_barrier();
 #pragma unroll 4
   for (int q = tid; q < l * l; q += 256) {
     const int k = q / l, j = q % l;
-    const double pk = s_row[k * P + k];
-    Uf[q] = j < k || !(pk > floor_) ? 0.0 : j == k ? sqrt(pk) : s_row[k * P + j] / sqrt(pk);
+    const double d = s_rt[k], r = s_ri[k], v = s_row[k * P + j];
+    double u = v * r;
+    u = fma(fma(-u, d, v), r, u);  // v / d, correctly rounded but for ties
+    Uf[q] = j < k || !(d > 0.0) ? 0.0 : j == k ? d : u;
   }
 }
 
@@ -405,13 +448,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 2))) voi
   }
 }
 
-// Round-robin pairing of lp elements: element 0 is fixed, the others rotate;
-// pair x of step `step` joins slots x and lp - 1 - x.
-__device__ __forceinline__ int rr_pos(int x, int step, int lp) {
-  const int y = x - 1 + step;
-  return x == 0 ? 0 : 1 + (y >= lp - 1 ? y - (lp - 1) : y);
-}
-
 // The rotation of a pair: t = sgn(tau) / (|tau| + sqrt(1 + tau^2)) for tau =
 // (aqq - app) / (2 apq), by half angles: two reciprocal square roots in the
 // dependent chain, no division.
@@ -444,21 +480,29 @@ __device__ __forceinline__ void jacobi_rot(double app, double aqq, double apq, d
   }
 }
 
-// Eigenvalues of the symmetric l x l M (padded with a zero row and column
-// when l is odd): cyclic Jacobi, round-robin pair order. Per step wavefront 0
-// computes the rotations and their pairs' own entries, while the other threads
-// read their 2 x 2 blocks (pair k1's rows, pair k2's columns, k1 < k2; only
-// entries (i, j) with i <= j are kept); after a barrier they apply both sides
-// of the rotation at once. The rotations go to
+// Eigenvalues of the symmetric l x l M (padded with zero rows and columns to lp
+// = jacobi_order(l)): cyclic Jacobi, round-robin pair order; only entries (i, j)
+// with i <= j are kept. A thread owns the 2 x 2 blocks (pair k1's rows, pair k2's
+// columns, k1 < k2) of a step and applies both sides of the rotation at once; a
+// rotation takes its pair in slot order.
+// From one step to the next every slot moves on by one, so each pair of the
+// next step has its entry in one block of this one: (0, 1), (x - 1, x + 1) and
+// (half - 2, half - 1), all different from 3 pairs on. Wavefront 0 owns these
+// blocks and turns the entry it has just rotated into the next step's rotation:
+// one barrier per step. The rotations go to
 // log[(sweep * (lp - 1) + step) * lp / 2 + pair] for k_jacobi_vec; meta: the
-// number of sweeps, then the eigenvalue order. Latency-bound (one workgroup,
-// (lp - 1) steps per sweep). Against the kernel that rotated rows, columns and
-// V in LDS in two passes: l = 74 1328 -> 480 us with the vectors' kernel.
+// number of sweeps, then the eigenvalue order. Bound by the step's dependent chain
+// (LDS reads, two rotations applied, two reciprocal square roots) and by one
+// compute unit's LDS (63 KB a step at l = 74). Against rotations formed between
+// two barriers: l = 74 412 -> 377 us.
+__host__ __device__ __forceinline__ int jacobi_order(int l) { return l <= 6 ? 6 : l + (l & 1); }
+
+template <int U>
 __global__ __launch_bounds__(1024) void k_jacobi(const double* __restrict__ Min, int l, int lp, double* __restrict__ w,
                                                  double2* __restrict__ log, int32_t* __restrict__ meta,
                                                  int max_sweeps) {
   extern __shared__ double s_m[];  // [lp][lp + 1], upper triangle (an odd pitch: rows and columns on distinct banks)
-  __shared__ double2 s_cs[64];
+  __shared__ double2 s_cs[2][64];
   __shared__ double s_red[16];
   const int pt = lp + 1;
   const int tid = threadIdx.x, nth = blockDim.x, lane = tid & 63, wave = tid >> 6;
@@ -485,135 +529,216 @@ __global__ __launch_bounds__(1024) void k_jacobi(const double* __restrict__ Min,
     return r;
   };
   const double norm0 = sumsq(true);
-  const int half = lp / 2, nblk = half * (half - 1) / 2;
-  // this thread's blocks (wavefronts 1 ..): pairs k1 < k2, at most 64 * 63 / 2 =
-  // 2016 blocks in 3 rounds of 960 threads
+  const int half = lp / 2, nrest = half * (half - 1) / 2 - half;
+  // this thread's blocks: wavefront 0 the next step's pairs, the other
+  // wavefronts the rest (pairs 1 apart but for the first and the last, and pairs
+  // 3 or more apart), at most 1952 blocks in U = 3 rounds of
+  // 960 threads (more registers than U = 1 leaves free)
   const int bth = nth - 64;
-  int kk[3];
+  int kk[U];
 #pragma unroll
-  for (int u = 0; u < 3; ++u) {
+  for (int u = 0; u < U; ++u) {
     int x = tid - 64 + u * bth;
     kk[u] = -1;
-    if (tid >= 64 && x < nblk) {
+    if (tid < half) {
+      if (u == 0) {
+        const int k1 = tid == 0 ? 0 : tid == half - 1 ? half - 2 : tid - 1;
+        const int k2 = tid == 0 ? 1 : tid == half - 1 ? half - 1 : tid + 1;
+        kk[u] = k1 | (k2 << 16);
+      }
+    } else if (tid >= 64 && x < half - 3) {
+      kk[u] = (1 + x) | ((2 + x) << 16);
+    } else if (tid >= 64 && x < nrest) {
+      x -= half - 3;
       int k1 = 0;
-      while (x >= half - 1 - k1) {
-        x -= half - 1 - k1;
+      while (x >= half - 3 - k1) {
+        x -= half - 3 - k1;
         ++k1;
       }
-      kk[u] = k1 | ((k1 + 1 + x) << 16);
+      kk[u] = k1 | ((k1 + 3 + x) << 16);
     }
   }
+  // Byte offsets: ec = 8 * element of the blocks' slots (first and second of
+  // either pair), moved on by one element with every step (element 0 stays);
+  // entry (i, j) lies at the smaller of (i, j)'s and (j, i)'s offset.
+  auto addr = [&](int ci, int cj) { return min(__mul24(ci, pt) + cj, __mul24(cj, pt) + ci); };
+  auto ent = [&](int off) -> double& { return *(double*)((char*)s_m + off); };
+  int ec[U][4], at[U][4];
+  auto locate = [&]() {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      at[u][0] = addr(ec[u][0], ec[u][2]);
+      at[u][1] = addr(ec[u][0], ec[u][3]);
+      at[u][2] = addr(ec[u][1], ec[u][2]);
+      at[u][3] = addr(ec[u][1], ec[u][3]);
+    }
+  };
+  // wavefront 0: the diagonal entries of the pair that the next step joins
+  // (first slot, second slot)
+  int df = 0, ds = 0;
+  const bool x_first = tid == 0, x_last = tid == half - 1;
+  auto diag = [&](int c) { return c * pt + c; };
+  auto next_pair = [&]() {
+    df = diag(x_first ? ec[0][0] : x_last ? ec[0][3] : ec[0][2]);
+    ds = diag(x_first ? ec[0][2] : ec[0][1]);
+  };
+  auto rotate = [&](int sweep, int step, double aff, double ass, double afs, int off) {
+    double c, s, t;
+    jacobi_rot(aff, ass, afs, c, s, t);
+    s_cs[step & 1][tid] = make_double2(c, s);
+    ent(df) = aff - t * afs;
+    ent(ds) = ass + t * afs;
+    ent(off) = 0.0;
+    log[(int64_t)(sweep * (lp - 1) + step) * half + tid] = make_double2(c, s);
+  };
+  if (wave == 0) __builtin_amdgcn_s_setprio(3);  // the chain of rotations
   int sweep = 0;
   for (; sweep < max_sweeps; ++sweep) {
     if (!(sumsq(false) > 1e-30 * norm0)) break;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {  // slot x holds element x
+      const int k1 = kk[u] & 0xFFFF, k2 = kk[u] >> 16;
+      ec[u][0] = 8 * k1;
+      ec[u][1] = 8 * (lp - 1 - k1);
+      ec[u][2] = 8 * k2;
+      ec[u][3] = 8 * (lp - 1 - k2);
+    }
+    locate();
+    if (tid < half) {
+      const int cf = 8 * tid, cs = 8 * (lp - 1 - tid), off = addr(cf, cs);
+      df = diag(cf);
+      ds = diag(cs);
+      rotate(sweep, 0, ent(df), ent(ds), ent(off), off);
+      next_pair();
+    }
+    lds_barrier();
     for (int step = 0; step < lp - 1; ++step) {
-      int at[3][4];
-      double m[3][4];
+      double m[U][4];
+      double2 e1[U], e2[U];
+      double aff = 0.0, ass = 0.0;
+      auto read = [&](int u) {
+        e1[u] = s_cs[step & 1][kk[u] & 0xFFFF];
+        e2[u] = s_cs[step & 1][kk[u] >> 16];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) m[u][v] = ent(at[u][v]);
+      };
+      if (U == 1 && kk[0] >= 0) read(0);
       if (tid < half) {
-        const int a = rr_pos(tid, step, lp), b = rr_pos(lp - 1 - tid, step, lp);
-        const int p = a < b ? a : b, q = a < b ? b : a;
-        const double app = s_m[p * pt + p], aqq = s_m[q * pt + q], apq = s_m[p * pt + q];
-        double c, s, t;
-        jacobi_rot(app, aqq, apq, c, s, t);
-        s_cs[tid] = make_double2(c, s);
-        s_m[p * pt + p] = app - t * apq;
-        s_m[q * pt + q] = aqq + t * apq;
-        s_m[p * pt + q] = 0.0;
-        log[(int64_t)(sweep * (lp - 1) + step) * half + tid] = make_double2(c, s);
-      } else {
-#pragma unroll
-        for (int u = 0; u < 3; ++u) {
-          if (kk[u] < 0) continue;
-          const int k1 = kk[u] & 0xFFFF, k2 = kk[u] >> 16;
-          const int a1 = rr_pos(k1, step, lp), b1 = rr_pos(lp - 1 - k1, step, lp);
-          const int a2 = rr_pos(k2, step, lp), b2 = rr_pos(lp - 1 - k2, step, lp);
-          const int p1 = min(a1, b1), q1 = max(a1, b1), p2 = min(a2, b2), q2 = max(a2, b2);
-          auto ix = [&](int i, int j) { return min(i, j) * pt + max(i, j); };
-          at[u][0] = ix(p1, p2);
-          at[u][1] = ix(p1, q2);
-          at[u][2] = ix(q1, p2);
-          at[u][3] = ix(q1, q2);
-#pragma unroll
-          for (int v = 0; v < 4; ++v) m[u][v] = s_m[at[u][v]];
-        }
+        aff = ent(df);
+        ass = ent(ds);
       }
-      lds_barrier();
 #pragma unroll
-      for (int u = 0; u < 3; ++u) {
+      for (int u = 0; u < U; ++u) {
+        if (U > 1) __builtin_amdgcn_sched_barrier(0);  // (a round at a time: all rounds' values would spill)
         if (kk[u] < 0) continue;
-        const double2 e1 = s_cs[kk[u] & 0xFFFF], e2 = s_cs[kk[u] >> 16];
-        const double app = e1.x * m[u][0] - e1.y * m[u][2], aqp = e1.y * m[u][0] + e1.x * m[u][2];
-        const double apq = e1.x * m[u][1] - e1.y * m[u][3], aqq = e1.y * m[u][1] + e1.x * m[u][3];
-        s_m[at[u][0]] = e2.x * app - e2.y * apq;
-        s_m[at[u][1]] = e2.y * app + e2.x * apq;
-        s_m[at[u][2]] = e2.x * aqp - e2.y * aqq;
-        s_m[at[u][3]] = e2.y * aqp + e2.x * aqq;
+        if (U > 1) read(u);
+        const double xff = e1[u].x * m[u][0] - e1[u].y * m[u][2], xsf = e1[u].y * m[u][0] + e1[u].x * m[u][2];
+        const double xfs = e1[u].x * m[u][1] - e1[u].y * m[u][3], xss = e1[u].y * m[u][1] + e1[u].x * m[u][3];
+        m[u][0] = e2[u].x * xff - e2[u].y * xfs;
+        m[u][1] = e2[u].y * xff + e2[u].x * xfs;
+        m[u][2] = e2[u].x * xsf - e2[u].y * xss;
+        m[u][3] = e2[u].y * xsf + e2[u].x * xss;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) ent(at[u][v]) = m[u][v];
       }
+      if (tid < half && step + 1 < lp - 1)
+        rotate(sweep, step + 1, aff, ass, x_first ? m[0][0] : x_last ? m[0][3] : m[0][2],
+               x_first ? at[0][0] : x_last ? at[0][3] : at[0][2]);
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int c = ec[u][v] + (v == 0 && (kk[u] & 0xFFFF) == 0 ? 0 : 8);
+          ec[u][v] = c == 8 * lp ? 8 : c;
+        }
+      locate();
+      if (tid < half) next_pair();
       lds_barrier();
     }
   }
-  // descending order (ties: lower index first), the first l kept
+  // descending order (ties: lower index first; the padding last), the first l
+  // kept
   if (tid < lp) {
     const double e = s_m[tid * pt + tid];
     int rank = 0;
-    for (int j = 0; j < lp; ++j) {
-      const double o = s_m[j * pt + j];
-      if (o > e || (o == e && j < tid)) ++rank;
+    if (tid >= l) {
+      rank = tid;
+    } else {
+      for (int j = 0; j < l; ++j) {
+        const double o = s_m[j * pt + j];
+        if (o > e || (o == e && j < tid)) ++rank;
+      }
+      w[rank] = e;
     }
     meta[1 + rank] = tid;
-    if (rank < l) w[rank] = e;
   }
   if (tid == 0) meta[0] = sweep;
 }
 
+// Value of the next lane (lane 63: 0), of the lane before (lane 0: 0).
+__device__ __forceinline__ double lane_above(double x) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, x);
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, 0x130, 0xf, 0xf, false);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), 0x130, 0xf, 0xf, false);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ double lane_below(double x) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, x);
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, 0x138, 0xf, 0xf, false);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), 0x138, 0xf, 0xf, false);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
 // Eigenvectors from k_jacobi's rotation log: row i of V = e_i J_1 J_2 ..., one
-// wavefront per row (the rows are independent), the row in LDS, the log
-// streamed a few steps ahead. Writes row i of the sorted Vs [l][l], and
-// workgroup 0 the singular values (square roots of the r largest eigenvalues).
-constexpr int kJacAhead = 8;
+// wavefront per row (the rows are independent). Lane x holds slots x and lp - 1 -
+// x of the row in registers and the slots move on by lane shifts (DPP); the
+// log is streamed kJacAhead steps ahead. A sweep's lp - 1 steps bring every
+// element back to the slot of its number. Writes row i of the sorted Vs [l][l],
+// and workgroup 0 the singular values (square roots of the r largest
+// eigenvalues). Bound by the chain of a product, an FMA and a shift per step;
+// against the row in LDS: l = 74 88 -> 38 us.
+constexpr int kJacAhead = 32;
 
 __global__ __launch_bounds__(64) void k_jacobi_vec(const double2* __restrict__ log, const int32_t* __restrict__ meta,
                                                    int l, int lp, const double* __restrict__ lam, int r,
                                                    double* __restrict__ Vs, double* __restrict__ sig,
                                                    double* __restrict__ sigma) {
-  __shared__ double s_v[128];
+  __shared__ double s_v[128];  // elements by number
   const int lane = threadIdx.x, row = blockIdx.x, half = lp / 2;
   if (row == 0)
     for (int i = lane; i < r; i += 64) sig[i] = sigma[i] = sqrt(lam[i] > 0.0 ? lam[i] : 0.0);
-  for (int j = lane; j < lp; j += 64) s_v[j] = j == row ? 1.0 : 0.0;
   const int nsteps = meta[0] * (lp - 1);
-  const bool on = lane < half;
+  const int x = lane < half ? lane : half - 1;  // (the lanes past the pairs repeat the last; nothing reads them)
+  double va = x == row ? 1.0 : 0.0, vb = lp - 1 - x == row ? 1.0 : 0.0;
+  const bool first = x == 0, last = x == half - 1;
   double2 cur[kJacAhead], nxt[kJacAhead];
   auto fetch = [&](double2* e, int s0) {
 #pragma unroll
-    for (int u = 0; u < kJacAhead; ++u)
-      if (on && s0 + u < nsteps) e[u] = log[(int64_t)(s0 + u) * half + lane];
+    for (int u = 0; u < kJacAhead; ++u) e[u] = log[(int64_t)(s0 + u < nsteps ? s0 + u : nsteps - 1) * half + x];
   };
-  fetch(cur, 0);
-  int step = 0;  // of the sweep
+  if (nsteps > 0) fetch(cur, 0);
   for (int s0 = 0; s0 < nsteps; s0 += kJacAhead) {
     fetch(nxt, s0 + kJacAhead);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int u = 0; u < kJacAhead; ++u) {
       if (s0 + u < nsteps) {
-        if (on) {
-          const int a = rr_pos(lane, step, lp), b = rr_pos(lp - 1 - lane, step, lp);
-          const int p = a < b ? a : b, q = a < b ? b : a;
-          const double vp = s_v[p], vq = s_v[q];
-          s_v[p] = cur[u].x * vp - cur[u].y * vq;
-          s_v[q] = cur[u].y * vp + cur[u].x * vq;
-        }
-        // one wavefront: its LDS accesses execute in order; keep the
-        // compiler from reordering steps
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_wave_barrier();
-        step = step + 1 == lp - 1 ? 0 : step + 1;
+        const double c = cur[u].x, s = cur[u].y;
+        const double na = c * va - s * vb, nb = s * va + c * vb;
+        const double up = lane_above(na), dn = lane_below(nb);
+        va = first ? na : last ? nb : up;
+        vb = first ? up : dn;
       }
     }
 #pragma unroll
     for (int u = 0; u < kJacAhead; ++u) cur[u] = nxt[u];
   }
-  for (int j = lane; j < l; j += 64) Vs[(int64_t)row * l + j] = s_v[meta[1 + j]];
+  if (lane < half) {
+    s_v[lane] = va;
+    s_v[lp - 1 - lane] = vb;
+  }
+  lds_barrier();
+  for (int j = lane; j < l; j += 64) Vs[(int64_t)row * l + j] = s_v[meta[1 + j] & 127];
 }
 
 // The symmetric split of the singular values over a product of S partials
@@ -716,7 +841,9 @@ hipError_t allow_lds_nb() {
 }
 hipError_t allow_lds() {
   static hipError_t e = [] {
-    hipError_t r = hipFuncSetAttribute((const void*)k_jacobi, hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 129 * 8);
+    hipError_t r = hipFuncSetAttribute((const void*)k_jacobi<1>, hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 129 * 8);
+    if (r == hipSuccess)
+      r = hipFuncSetAttribute((const void*)k_jacobi<3>, hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 129 * 8);
     if (r == hipSuccess)
       r = hipFuncSetAttribute((const void*)k_dgemm<double, 2, 2, 2, 2>, hipFuncAttributeMaxDynamicSharedMemorySize,
                               dg_lds(4, 4));
@@ -741,12 +868,13 @@ hipError_t allow_lds() {
 // under k_chol's pivot floor: enough between the products of the subspace
 // iteration, where only the span and its conditioning count. Two passes
 // (CholeskyQR2) make it orthonormal to rounding, which the final basis is. The
-// Gram matrix's K is split at most 8 ways: k_chol's one workgroup reads the
-// partials.
+// Gram matrix's K is split at most 16 ways (8 past l = 80, where k_chol loads
+// fewer partials together): k_chol's one workgroup reads the partials. 2048 rows,
+// l = 74, 8 -> 16 ways: Gram matrix 24 -> 14 us.
 hipError_t cholqr(double* Y, int rows, int l, int passes, double* U, hipStream_t s, double* part) {
+  const int nb = (l + 15) / 16;
   for (int pass = 0; pass < passes; ++pass) {
-    const int S = dgemm_parts(l, l, rows, (const double*)Y, l, 1, (const double*)Y, l, 0, part, part, kDgParts, s, 8);
-    const int nb = (l + 15) / 16;
+    const int S = dgemm_parts(l, l, rows, (const double*)Y, l, 1, (const double*)Y, l, 0, part, part, kDgParts, s, nb <= 5 ? 16 : 8);
     const dim3 gt((rows + kTrsmRows - 1) / kTrsmRows);
     switch (nb) {
 #define LX_CASE(NB)                                                                                            \
@@ -770,12 +898,12 @@ hipError_t cholqr(double* Y, int rows, int l, int passes, double* U, hipStream_t
 hipError_t factors_from_sketch(int rows, int cols, int r, int l, const double* Y, const double* T, const double* Gm,
                                double* lam, double* Ve, double* sig, double* Ad, double* Bd, float* A, float* B,
                                double* sigma, hipStream_t s, double* part) {
-  const int lp = l + (l & 1), half = lp / 2;
+  const int lp = jacobi_order(l), half = lp / 2;
   int32_t* const meta = (int32_t*)(part + kDgParts - 128);
-  const int nblk = half * (half - 1) / 2;
-  const int nth = 64 + std::min(960, (nblk + 63) / 64 * 64);  // wavefront 0 and the blocks' threads
-  hipLaunchKernelGGL(k_jacobi, dim3(1), dim3(std::max(nth, 128)), (size_t)lp * (lp + 1) * sizeof(double), s, Gm, l, lp, lam,
-                     (double2*)part, meta, kMaxSweeps);
+  const int nrest = half * (half - 1) / 2 - half;
+  const int nth = 64 + std::min(960, (nrest + 63) / 64 * 64);  // wavefront 0 and the other blocks' threads
+  hipLaunchKernelGGL(nrest <= 960 ? k_jacobi<1> : k_jacobi<3>, dim3(1), dim3(std::max(nth, 128)),
+                     (size_t)lp * (lp + 1) * sizeof(double), s, Gm, l, lp, lam, (double2*)part, meta, kMaxSweeps);
   hipLaunchKernelGGL(k_jacobi_vec, dim3(l), dim3(64), 0, s, (const double2*)part, meta, l, lp, lam, r, Ve, sig, sigma);
   int S = dgemm_parts(rows, r, l, Y, l, 0, (const double*)Ve, l, 0, Ad, part, kDgParts, s);
   hipLaunchKernelGGL(k_split_f32, dim3(blocks((int64_t)rows * r)), dim3(256), 0, s,

@@ -197,6 +197,15 @@ def test_factors_at_the_sketch_width_edges(rows, cols, r, p):
     assert np.all(np.diff(sig) <= 0)
 
 
+@pytest.mark.parametrize("l", [2, 3, 5, 6, 7, 8, 10, 32, 33, 80, 90, 91])
+def test_factors_at_the_jacobi_edges(l):
+    """Sketch widths at and below the padded order of the eigenvalue kernel (6),
+    the first with every kind of next pair (order 8 and 10), both sides of its
+    one-block-per-thread limit (order 90 and 92), and the Cholesky kernel's
+    16-column blocks filled and just begun."""
+    test_factors_at_the_sketch_width_edges(120, 150, max(1, l - 2), l - max(1, l - 2))
+
+
 def test_factors_of_an_exactly_low_rank_residual():
     """More sketch columns than the residual's rank: the columns it does not
     have carry nothing, and A B is the residual."""

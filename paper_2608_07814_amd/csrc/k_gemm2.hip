@@ -1116,7 +1116,7 @@ __device__ __forceinline__ float load_dev(const float* p) {
 // is fetched once. Rings: 4
 // stages of 12 KB or 3 of 16 KB (three workgroups per compute unit, two or
 // three steps in flight while one is consumed), 2 stages for products of at
-// most two steps. With few rows per tile the kernel streams weights and is
+// most two steps (12 KB stages; 16 KB for hi/lo pairs of two weight slabs). With few rows per tile the kernel streams weights and is
 // bound by HBM, not by the MFMAs. A product with few output tiles and a long
 // K (e.g. a down projection at batch 1) is split along K so that enough
 // workgroups stream weight slabs at once; the partial tiles meet in the
@@ -1945,6 +1945,12 @@ hipError_t launch_gemm_skinny_batch(const GemmArgs* g, const int* ofmt, const in
   }
   if (pair && max_steps > 4) {
     hipLaunchKernelGGL((k_gemm_skinny<3, 2>), dim3(wg), dim3(SK_THR), 0, s, b);
+  } else if (pair && max_steps > 2) {
+    // at most two weight slabs: all of them in flight at once in 32 KB, five
+    // workgroups per compute unit instead of the 4-stage ring's three, and one
+    // fetch of a slab for both halves. Tree T = 16 (ranks 128 and 64), gate|up and
+    // down: 25 -> 21 and 47 -> 36 us
+    hipLaunchKernelGGL((k_gemm_skinny<2, 2>), dim3(wg), dim3(SK_THR), 0, s, b);
   } else if (max_steps <= 2) {
     hipLaunchKernelGGL((k_gemm_skinny<2, 1>), dim3(wg), dim3(SK_THR), 0, s, b);
   } else {

@@ -1116,8 +1116,9 @@ __device__ __forceinline__ float load_dev(const float* p) {
 // is fetched once. Rings: 4
 // stages of 12 KB or 3 of 16 KB (three workgroups per compute unit, two or
 // three steps in flight while one is consumed), 2 stages for products of at
-// most two steps (12 KB stages; 16 KB for hi/lo pairs of two weight slabs). With few rows per tile the kernel streams weights and is
-// bound by HBM, not by the MFMAs. A product with few output tiles and a long
+// most two steps (12 KB stages; 16 KB for hi/lo pairs of two weight slabs).
+// With few rows per tile the kernel streams weights and is bound by HBM, not by
+// the MFMAs. A product with few output tiles and a long
 // K (e.g. a down projection at batch 1) is split along K so that enough
 // workgroups stream weight slabs at once; the partial tiles meet in the
 // workspace and the last workgroup of a tile adds them.
@@ -1286,13 +1287,15 @@ __device__ __forceinline__ void sk_epilogue(const SkUnit& u, const f32x16& acc, 
   }
 }
 
+constexpr int skinny_lds(int nst, int per) { return nst * (per * kSkinnyBM + kSkinnyBN) * BK2; }
+constexpr int skinny_wide_lds(int nb, int per) { return (per * kSkinnyBM + nb * kSkinnyBN) * BK2; }
+
 template <int SK_NST, int PER>
-__global__ __launch_bounds__(SK_THR) void k_gemm_skinny(SkinnyBatch b) {
+__device__ __forceinline__ void skinny_body(const SkinnyBatch& b, u16* smem) {
   constexpr int BM = kSkinnyBM, BN = kSkinnyBN;
   constexpr int A_ROUNDS = BM * 8 / SK_THR, B_ROUNDS = BN * 8 / SK_THR;
   constexpr int R = PER * A_ROUNDS + B_ROUNDS;
   constexpr int SA = BM * BK2, STAGE = (PER * BM + BN) * BK2;
-  __shared__ __attribute__((aligned(1024))) u16 smem[SK_NST * STAGE];
 
   // A step of the K loop: PER == 1, one 64-wide slab of A's K (any nper);
   // PER == 2 (nper == 2), one weight slab, multiplied by both periods of A
@@ -1431,6 +1434,11 @@ __global__ __launch_bounds__(SK_THR) void k_gemm_skinny(SkinnyBatch b) {
   sk_epilogue(u, acc, (float*)smem + wave * (32 * 36));
 }
 
+template <int SK_NST, int PER>
+__global__ __launch_bounds__(SK_THR) void k_gemm_skinny(SkinnyBatch b) {
+  __shared__ __attribute__((aligned(1024))) u16 smem[skinny_lds(SK_NST, PER)];
+  skinny_body<SK_NST, PER>(b, smem);
+}
 
 // Wide variant for products whose K is one weight slab (K = 64, or a bf16
 // (hi, lo) pair against a 64-column weight row): a workgroup takes NB
@@ -1440,11 +1448,10 @@ __global__ __launch_bounds__(SK_THR) void k_gemm_skinny(SkinnyBatch b) {
 // is paid once per NB tiles. Wavefront w computes columns w * 32 .. w * 32 + 31
 // of each of its tiles.
 template <int NB, int PER>
-__global__ __launch_bounds__(SK_THR) void k_gemm_skinny_wide(SkinnyBatch b) {
+__device__ __forceinline__ void skinny_wide_body(const SkinnyBatch& b, u16* smem) {
   constexpr int BM = kSkinnyBM, BN = kSkinnyBN;
   constexpr int A_ROUNDS = BM * 8 / SK_THR, B_ROUNDS = BN * 8 / SK_THR;
   constexpr int SA = BM * BK2, SBt = BN * BK2;
-  __shared__ __attribute__((aligned(1024))) u16 smem[PER * SA + NB * SBt];
 
   int pi = 0;
   while (pi + 1 < b.n && (int)blockIdx.x >= b.base[pi + 1]) ++pi;
@@ -1546,6 +1553,27 @@ __global__ __launch_bounds__(SK_THR) void k_gemm_skinny_wide(SkinnyBatch b) {
     sk_epilogue(u, acc[t], ep);
     bar();  // ep is rewritten by the next tile
   }
+}
+
+template <int NB, int PER>
+__global__ __launch_bounds__(SK_THR) void k_gemm_skinny_wide(SkinnyBatch b) {
+  __shared__ __attribute__((aligned(1024))) u16 smem[skinny_wide_lds(NB, PER)];
+  skinny_wide_body<NB, PER>(b, smem);
+}
+
+// Hi/lo products of one weight slab (wide) and of two in one launch: a tree's
+// leaf and intermediate low-rank outputs. Bound by the latency of a workgroup's
+// few loads, so the one-slab products' workgroups take four column tiles. Tree
+// T = 16, gate|up 21 -> 19 us, down 36 -> 31 us.
+__global__ __launch_bounds__(SK_THR) void k_gemm_skinny_mix(SkinnyBatch b) {
+  constexpr int ring = skinny_lds(2, 2), row = skinny_wide_lds(4, 2), lds = ring > row ? ring : row;
+  __shared__ __attribute__((aligned(1024))) u16 smem[lds];
+  int pi = 0;
+  while (pi + 1 < b.n && (int)blockIdx.x >= b.base[pi + 1]) ++pi;
+  if ((b.wide_mask >> pi) & 1)
+    skinny_wide_body<4, 2>(b, smem);
+  else
+    skinny_body<2, 2>(b, smem);
 }
 
 template <int BM, int BN>
@@ -1918,15 +1946,16 @@ hipError_t launch_gemm_skinny_batch(const GemmArgs* g, const int* ofmt, const in
   // tiles that 4-tile groups still give at least 512 workgroups: wide
   // (with few row tiles, e.g. one token, the narrow kernel keeps more
   // workgroups, hence more loads, in flight)
-  bool wide = true;
-  int64_t groups = 0;
-  for (int i = 0; i < n; ++i) groups += (int64_t)grid_tiles[i] * ((b.ntn[i] + 3) / 4);
-  wide = groups >= 512;
-  for (int i = 0; i < n; ++i) {
+  auto groups_of = [&](int i) { return (int64_t)grid_tiles[i] * ((b.ntn[i] + 3) / 4); };
+  auto one_slab = [&](int i) {
     const int Kb = g[i].Kb > 0 ? g[i].Kb : g[i].K;
-    wide = wide && Kb == BK2 && (g[i].K == BK2 || g[i].K == 2 * BK2) && g[i].K == g[0].K && g[i].split_force <= 1 &&
+    return Kb == BK2 && (g[i].K == BK2 || g[i].K == 2 * BK2) && g[i].split_force <= 1 &&
            (g[i].ncols[1] == 0 || g[i].a_koff[0] == g[i].a_koff[1] || g[i].ncols[0] % (4 * kSkinnyBN) == 0);
-  }
+  };
+  int64_t groups = 0;
+  for (int i = 0; i < n; ++i) groups += groups_of(i);
+  bool wide = groups >= 512;
+  for (int i = 0; i < n; ++i) wide = wide && one_slab(i) && g[i].K == g[0].K;
   if (wide) {
     SkinnyBatch bw = b;
     int wgw = 0;
@@ -1950,7 +1979,21 @@ hipError_t launch_gemm_skinny_batch(const GemmArgs* g, const int* ofmt, const in
     // workgroups per compute unit instead of the 4-stage ring's three, and one
     // fetch of a slab for both halves. Tree T = 16 (ranks 128 and 64), gate|up and
     // down: 25 -> 21 and 47 -> 36 us
-    hipLaunchKernelGGL((k_gemm_skinny<2, 2>), dim3(wg), dim3(SK_THR), 0, s, b);
+    // (products of one slab among them, if large enough to fill the chip: wide)
+    SkinnyBatch bm = b;
+    int wgm = 0;
+    for (int i = 0; i < n; ++i) {
+      const bool w = one_slab(i) && groups_of(i) >= 512;
+      bm.wide_mask |= w ? 1 << i : 0;
+      bm.base[i] = wgm;
+      wgm += w ? (int)((groups_of(i) + NXCD - 1) / NXCD * NXCD)
+               : skinny_grid(g[i], (int64_t)grid_tiles[i] * b.ntn[i]);
+    }
+    bm.base[n] = wgm;
+    if (bm.wide_mask)
+      hipLaunchKernelGGL(k_gemm_skinny_mix, dim3(wgm), dim3(SK_THR), 0, s, bm);
+    else
+      hipLaunchKernelGGL((k_gemm_skinny<2, 2>), dim3(wg), dim3(SK_THR), 0, s, b);
   } else if (max_steps <= 2) {
     hipLaunchKernelGGL((k_gemm_skinny<2, 1>), dim3(wg), dim3(SK_THR), 0, s, b);
   } else {

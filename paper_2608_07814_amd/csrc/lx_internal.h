@@ -418,6 +418,7 @@ struct SkinnyBatch {
   int32_t ofmt[kSkinnyMaxProblems];  // OutFmt
   int32_t base[kSkinnyMaxProblems + 1];  // first workgroup of each problem
   int32_t n;
+  int32_t wide_mask;  // k_gemm_skinny_mix: problems in 4-tile column groups
 };
 hipError_t launch_gemm_skinny_batch(const GemmArgs* g, const int* ofmt, const int* grid_tiles, int n,
                                     hipStream_t s);

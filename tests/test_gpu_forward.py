@@ -177,6 +177,19 @@ def test_cfg4_tree_small():
     assert e <= TOL_DESIGN
 
 
+@pytest.mark.parametrize("over,T", [({}, 1), ({}, 7), ({}, 17), ({"d": 320, "f": 192}, 40), ({"d": 576, "f": 256}, 64)])
+def test_tree_decode_on_the_two_slab_kernels(over, T):
+    """Small tree batches, whose sub and leaf levels' outputs (ranks 128 and 64,
+    hi and lo halves) share a launch: too few leaf tiles for 4-tile column
+    groups (T=1), enough, column counts that end inside a group, and a gate|up
+    boundary inside one (those products keep single tiles)."""
+    require_gpu()
+    p = make_problem(dict(config(4), **over), seed=T, T=T)
+    e = err_ratio(gpu_forward(p), _oracle(p))
+    say(f"tree {over} T={T}: err/RMS = {e:.3e}")
+    assert e <= TOL_BF16 and e <= TOL_DESIGN
+
+
 def test_cfg4_tree_mixed_kernels():
     """T=100: the root level runs on the large-tile kernel while the sub and
     leaf levels (few rows per node) run on the skinny kernel."""

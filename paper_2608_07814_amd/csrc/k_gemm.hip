@@ -310,13 +310,15 @@ __device__ __forceinline__ void f32_load_lds16(const void* gptr, const void* lds
                : "memory");
 }
 // s_waitcnt vmcnt(N) alone; barrier without a fence (each wavefront waits for
-// its own loads first)
+// its own loads first, and here for its own LDS reads: after the barrier
+// another wavefront's direct load overwrites the stage that they read)
 template <int N>
 __device__ __forceinline__ void f32_wait_vm() {
   __builtin_amdgcn_s_waitcnt((N & 0xF) | ((N >> 4) << 14) | (0x7 << 4) | (0xF << 8));
 }
 __device__ __forceinline__ void f32_bar() {
   asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0xF | (0x3 << 14) | (0x7 << 4));  // lgkmcnt(0)
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
 }

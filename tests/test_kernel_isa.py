@@ -1,0 +1,49 @@
+"""Waits that a kernel's source has to state itself, read from the gfx950 assembly
+that the sources compile to (no GPU needed)."""
+import os
+import re
+import subprocess
+
+from paper_2608_07814_amd import build as B
+
+
+def _asm(tmp_path, src):
+    out = str(tmp_path / (src + ".s"))
+    subprocess.run([B.HIPCC, *B.CFLAGS, "--cuda-device-only", "-S", os.path.join(B.CSRC, src), "-o", out],
+                   check=True, stderr=subprocess.DEVNULL)
+    return open(out).read()
+
+
+def _functions(asm):
+    """Name -> lines of every function."""
+    out, name = {}, None
+    for line in asm.splitlines():
+        m = re.match(r"(_Z\w+):", line)
+        if m:
+            name = m.group(1)
+            out[name] = []
+        elif line.startswith(".Lfunc_end"):
+            name = None
+        elif name:
+            out[name].append(line)
+    return out
+
+
+def test_fp32_ring_waits_for_lds_reads_before_freeing_a_stage(tmp_path):
+    """The K loop's barrier frees the stage of the slab before it for direct
+    loads of every wavefront, so each wavefront's LDS reads have to be
+    complete when it arrives: the wait stands right before the barrier."""
+    kernels = {n: f for n, f in _functions(_asm(tmp_path, "k_gemm.hip")).items() if "k_gemm_f32m" in n}
+    assert len(kernels) == 2
+    for name, lines in kernels.items():
+        in_loop, block, seen = False, [], 0
+        for line in lines:
+            if line.startswith(".LBB"):
+                in_loop, block = "Loop" in line, []
+                continue
+            block.append(line.split(";")[0].strip())
+            if block[-1] == "s_barrier" and in_loop:
+                waits = [b for b in block[:-1] if b.startswith("s_waitcnt")]
+                assert waits and "lgkmcnt(0)" in waits[-1], (name, block)
+                seen += 1
+        assert seen == 1, (name, seen)

@@ -25,6 +25,7 @@
 //     to a log. k_jacobi_vec: the eigenvectors from the log, one wavefront per
 //     row of V, eigenpairs sorted descending.
 #include "lx_internal.h"
+#include "lx_stage3_ws.h"
 
 #include <algorithm>
 
@@ -770,9 +771,6 @@ __global__ __launch_bounds__(256) void k_fill_act(const void* __restrict__ x, in
 
 inline unsigned blocks(int64_t n, int t = 256) { return (unsigned)((n + t - 1) / t); }
 
-// Partial products: at most kDgParts doubles. (The rotation log of k_jacobi
-// takes the same buffer: 40 sweeps of 127 steps of 64 rotations at most.)
-constexpr int64_t kDgParts = 384 * 64 * 64;
 constexpr int kMaxSweeps = 40;
 static_assert((int64_t)kMaxSweeps * 127 * 64 * 2 + 128 <= kDgParts, "the rotation log fits the partial products' buffer");
 
@@ -916,17 +914,9 @@ hipError_t factors_from_sketch(int rows, int cols, int r, int l, const double* Y
 
 }  // namespace
 
-size_t lowrank_ws_doubles(int rows, int cols, int l) {
-  const int lp = l + (l & 1);
-  return (size_t)rows * cols + (size_t)rows * l + (size_t)cols * l + (size_t)l * cols + 4 * (size_t)lp * lp + 2 * lp +
-         (size_t)rows * l + (size_t)kDgParts;
-}
+size_t lowrank_ws_doubles(int rows, int cols, int l) { return (size_t)stage3_ws(rows, cols, -1, l).total; }
 
-size_t weighted_ws_doubles(int rows, int cols, int np, int l) {
-  const int lp = l + (l & 1);
-  return (size_t)rows * cols + (size_t)np * cols + (size_t)cols * l + (size_t)rows * l + (size_t)np * l +
-         (size_t)l * cols + (size_t)l * np + 4 * (size_t)lp * lp + 2 * lp + (size_t)rows * l + (size_t)kDgParts;
-}
+size_t weighted_ws_doubles(int rows, int cols, int np, int l) { return (size_t)stage3_ws(rows, cols, np, l).total; }
 
 hipError_t launch_align_cost(const void* dg, const void* du, const void* dd, const void* mg, const void* mu,
                              const void* md, int bf16, int f, int d, double* cost, double* ws, hipStream_t s) {
@@ -950,19 +940,19 @@ hipError_t launch_align_cost(const void* dg, const void* du, const void* dd, con
 hipError_t launch_lowrank(const void* wd, const void* wm, int bf16, int rows, int cols, const int32_t* perm, int axis,
                           int r, int l, int q, const double* omega, float* A, float* B, double* sigma, double* ws,
                           hipStream_t s) {
-  const int lp = l + (l & 1);
   if (const hipError_t e0 = allow_lds(); e0 != hipSuccess) return e0;
-  double* const R = ws;                              // rows x cols
-  double* const Y = R + (size_t)rows * cols;         // rows x l
-  double* const Z = Y + (size_t)rows * l;            // cols x l
-  double* const Bs = Z + (size_t)cols * l;           // l x cols
-  double* const G = Bs + (size_t)l * cols;           // lp x lp (three of them)
-  double* const U = G + (size_t)lp * lp;
-  double* const Ve = U + (size_t)lp * lp;
-  double* const lam = Ve + (size_t)lp * lp;          // lp
-  double* const sig = lam + lp;                      // lp
-  double* const Ad = sig + lp;                       // rows x l (A before truncation)
-  double* const part = Ad + (size_t)rows * l;        // kDgParts (partial products)
+  const Stage3Ws w = stage3_ws(rows, cols, -1, l);
+  double* const R = ws + w.R;
+  double* const Y = ws + w.Y;
+  double* const Z = ws + w.Z;
+  double* const Bs = ws + w.T;
+  double* const G = ws + w.G;
+  double* const U = ws + w.U;
+  double* const Ve = ws + w.Ve;
+  double* const lam = ws + w.lam;
+  double* const sig = ws + w.sig;
+  double* const Ad = ws + w.Ad;
+  double* const part = ws + w.part;
   hipLaunchKernelGGL(k_residual, dim3(blocks((int64_t)rows * cols)), dim3(256), 0, s, wd, wm, bf16, rows, cols, perm,
                      axis, R);
   hipError_t e;
@@ -985,23 +975,23 @@ hipError_t launch_lowrank(const void* wd, const void* wm, int bf16, int rows, in
 hipError_t launch_weighted(const void* wd, const void* wm, int bf16, int rows, int cols, const int32_t* perm, int axis,
                            const void* x, int x_bf16, int n, double damp, int r, int l, int q, const double* omega,
                            float* A, float* B, double* sigma, double* ws, hipStream_t s) {
-  const int lp = l + (l & 1);
   const int np = n + (damp > 0.0 ? cols : 0);
   if (const hipError_t e0 = allow_lds(); e0 != hipSuccess) return e0;
-  double* const R = ws;                              // rows x cols
-  double* const Xp = R + (size_t)rows * cols;        // np x cols: [X; sqrt(damp) I]
-  double* const P = Xp + (size_t)np * cols;          // cols x l
-  double* const Y = P + (size_t)cols * l;            // rows x l
-  double* const Z = Y + (size_t)rows * l;            // np x l
-  double* const T = Z + (size_t)np * l;              // l x cols
-  double* const Wt = T + (size_t)l * cols;           // l x np
-  double* const G = Wt + (size_t)l * np;             // lp x lp (three of them)
-  double* const U = G + (size_t)lp * lp;
-  double* const Ve = U + (size_t)lp * lp;
-  double* const lam = Ve + (size_t)lp * lp;          // lp
-  double* const sig = lam + lp;                      // lp
-  double* const Ad = sig + lp;                       // rows x l
-  double* const part = Ad + (size_t)rows * l;        // kDgParts
+  const Stage3Ws w = stage3_ws(rows, cols, np, l);
+  double* const R = ws + w.R;
+  double* const Xp = ws + w.Xp;  // [X; sqrt(damp) I]
+  double* const P = ws + w.P;
+  double* const Y = ws + w.Y;
+  double* const Z = ws + w.Z;
+  double* const T = ws + w.T;
+  double* const Wt = ws + w.Wt;
+  double* const G = ws + w.G;
+  double* const U = ws + w.U;
+  double* const Ve = ws + w.Ve;
+  double* const lam = ws + w.lam;
+  double* const sig = ws + w.sig;
+  double* const Ad = ws + w.Ad;
+  double* const part = ws + w.part;
   hipLaunchKernelGGL(k_residual, dim3(blocks((int64_t)rows * cols)), dim3(256), 0, s, wd, wm, bf16, rows, cols, perm,
                      axis, R);
   hipLaunchKernelGGL(k_fill_act, dim3(blocks((int64_t)np * cols)), dim3(256), 0, s, x, x_bf16, n, cols, sqrt(damp),

@@ -18,6 +18,7 @@
 //     order, ties to the lower index) until no medoid moves. Per-cluster
 //     minima in LDS with 64-bit atomic min on order-preserving keys, so every
 //     decision is the exact fp64 comparison a sequential loop would make.
+#include "lx_device_once.h"
 #include "lx_internal.h"
 
 #include <algorithm>
@@ -412,9 +413,14 @@ hipError_t launch_kmedoids(const double* dist, const uint32_t* fire, int E, int 
                            int max_iter, int32_t* cluster_of, int32_t* factor_of, int32_t* dominant,
                            int32_t* iterations, hipStream_t s) {
   if (E <= kKmSmall) {
-    static const hipError_t lds = hipFuncSetAttribute((const void*)k_kmedoids<kKmSmall>,
-                                                      hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                      kKmSmall * (kKmSmall | 1) * 8);
+    static DeviceOnce once;
+    int dev = 0;
+    hipError_t lds = hipGetDevice(&dev);
+    if (lds == hipSuccess)
+      lds = once.run(dev, hipSuccess, [] {
+        return hipFuncSetAttribute((const void*)k_kmedoids<kKmSmall>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                   kKmSmall * (kKmSmall | 1) * 8);
+      });
     if (lds != hipSuccess) return lds;
     hipLaunchKernelGGL(k_kmedoids<kKmSmall>, dim3(1), dim3(512), (size_t)E * (E | 1) * 8, s, dist, fire, E, C, pm, P,
                        max_iter, cluster_of, factor_of, dominant, iterations);

@@ -24,6 +24,7 @@
 //     rotates l / 2 disjoint pairs at once; matrix in LDS, rotations written
 //     to a log. k_jacobi_vec: the eigenvectors from the log, one wavefront per
 //     row of V, eigenpairs sorted descending.
+#include "lx_device_once.h"
 #include "lx_internal.h"
 #include "lx_stage3_ws.h"
 
@@ -824,7 +825,7 @@ hipError_t dgemm(int M, int N, int K, const double* A, int64_t lda, int ta, cons
   return hipGetLastError();
 }
 
-// Kernels with more than 64 KB of dynamic LDS: allow it once per process.
+// Kernels with more than 64 KB of dynamic LDS: allow it, once per device.
 template <int NB>
 hipError_t allow_lds_nb() {
   const hipFuncAttribute a = hipFuncAttributeMaxDynamicSharedMemorySize;
@@ -838,7 +839,10 @@ hipError_t allow_lds_nb() {
   return r;
 }
 hipError_t allow_lds() {
-  static hipError_t e = [] {
+  static DeviceOnce once;
+  int dev = 0;
+  if (const hipError_t e = hipGetDevice(&dev); e != hipSuccess) return e;
+  return once.run(dev, hipSuccess, [] {
     hipError_t r = hipFuncSetAttribute((const void*)k_jacobi<1>, hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 129 * 8);
     if (r == hipSuccess)
       r = hipFuncSetAttribute((const void*)k_jacobi<3>, hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 129 * 8);
@@ -857,8 +861,7 @@ hipError_t allow_lds() {
     if (r == hipSuccess) r = allow_lds_nb<7>();
     if (r == hipSuccess) r = allow_lds_nb<8>();
     return r;
-  }();
-  return e;
+  });
 }
 
 // Y (rows x l) <- Y U^-1, U the Cholesky factor of its Gram matrix; U: l x l

@@ -60,15 +60,6 @@ __device__ __forceinline__ void add4(float4& a, const float4& b) {
   a.w += b.w;
 }
 __device__ __forceinline__ float silu_mul(float g, float u) { return g / (1.f + expf(-g)) * u; }
-// The same with the hardware exponential and reciprocal (each good to a few
-// units in the last place of fp32), for gate|up rows that were rounded to x16
-// anyway (2^-14 of a group's maximum): a third of the instructions, and the
-// SwiGLU kernels are bound by theirs. With each row's sum formed once instead of
-// per pass: flat T = 4096 80 -> 61 us, tree T = 8192 141 -> 117 us, dense T = 2048
-// 32 -> 20 us.
-__device__ __forceinline__ float silu_mul_fast(float g, float u) {
-  return g * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(g * -1.44269504f)) * u;
-}
 
 // hbar row segment (4 neurons at column c), rows of 4f bytes: fp32; or a
 // bf16 (hi, lo) pair (hi half, lo half); or bf16 hi, fp8 lo and one E8M0
@@ -367,7 +358,7 @@ __global__ __launch_bounds__(kFastThr) void k_swiglu_fast(TokenArgs a) {
       add4(g, cvt<X16>(gv[j][l], c));
       add4(u, cvt<X16>(uv[j][l], f + c));
     }
-    auto act = [&](float x, float y) { return w[j] * (X16 ? silu_mul_fast(x, y) : silu_mul(x, y)); };
+    auto act = [&](float x, float y) { return w[j] * silu_mul(x, y); };
     h[j] = make_float4(act(g.x, u.x), act(g.y, u.y), act(g.z, u.z), act(g.w, u.w));
   }
   // each level-l row that does work: the sum of its experts' h in slot order
@@ -375,7 +366,9 @@ __global__ __launch_bounds__(kFastThr) void k_swiglu_fast(TokenArgs a) {
   // rows' sums, so only the anchor and leaf levels are stored)
   auto stored = [&](int l, int j0) { return (fl[l][j0] & 3) == 3 && !(merged && l > 0 && l < NL); };
   // (the leaf level's rows are the distinct experts: h itself; the others are
-  // summed once and kept)
+  // summed once and kept, not once per pass: the kernel is bound by its
+  // instructions; flat T = 4096 78 -> 70 us, tree T = 8192 136 -> 126 us, dense
+  // T = 2048 28 -> 26 us)
   float4 hs[NL > 0 ? NL : 1][kFastK];
 #pragma unroll
   for (int l = 0; l < NL; ++l)
@@ -475,8 +468,8 @@ __global__ __launch_bounds__(kFastThr) void k_swiglu_x16w(TokenArgs a) {
     }
 #pragma unroll
     for (int q = 0; q < 2; ++q)
-      h[j][q] = make_float4(w[j] * silu_mul_fast(g[q].x, u[q].x), w[j] * silu_mul_fast(g[q].y, u[q].y),
-                            w[j] * silu_mul_fast(g[q].z, u[q].z), w[j] * silu_mul_fast(g[q].w, u[q].w));
+      h[j][q] = make_float4(w[j] * silu_mul(g[q].x, u[q].x), w[j] * silu_mul(g[q].y, u[q].y),
+                            w[j] * silu_mul(g[q].z, u[q].z), w[j] * silu_mul(g[q].w, u[q].w));
   }
   auto stored = [&](int l, int j0) { return (fl[l][j0] & 3) == 3 && !(merged && l > 0 && l < NL); };
   // (the leaf level's rows are the distinct experts: h itself; the others are

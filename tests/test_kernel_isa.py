@@ -47,3 +47,15 @@ def test_fp32_ring_waits_for_lds_reads_before_freeing_a_stage(tmp_path):
                 assert waits and "lgkmcnt(0)" in waits[-1], (name, block)
                 seen += 1
         assert seen == 1, (name, seen)
+
+
+def test_swiglu_divides(tmp_path):
+    """SiLU in full fp32, whatever format the rows have: every exponential of a
+    SwiGLU kernel has its range reduction, and its division the IEEE fix-up
+    (a bare hardware exponential and reciprocal are off by 8e-7 at g = -25)."""
+    kernels = {n: "\n".join(f) for n, f in _functions(_asm(tmp_path, "k_token.hip")).items() if "k_swiglu" in n}
+    assert len(kernels) >= 10
+    for name, code in kernels.items():
+        n = len(re.findall(r"\bv_exp_f32", code))
+        assert n > 0 and n == len(re.findall(r"\bv_div_fixup_f32", code)), name
+        assert n <= len(re.findall(r"\bv_rndne_f32", code)), name

@@ -25,6 +25,7 @@
 #include <vector>
 
 #include "lx_internal.h"
+#include "lx_tiles.h"
 
 namespace lx {
 namespace {
@@ -157,41 +158,10 @@ struct Plan {
 
 int level_nodes(const lx_tree_layer& t, int l) { return l == 0 ? t.n_anchors : t.levels[l - 1].n_nodes; }
 
-// Tile shape (bm x bn) of a bf16 product of `ncol` columns and depth K over a
-// level's rows on the large-tile kernel; returns its predicted time in us.
-// 256 x 256 tiles do the most MFMA work per byte staged and are kept
-// where they give every compute unit an item. With fewer items (mid-sized
-// batches: rows of tens of nodes and a few hundred tokens) a launch lasts as
-// long as one item, so smaller tiles win; each shape's time per 64-wide slab
-// and per item, and the number of rounds of 256 items, decide. Measured (the
-// largest tile against the chosen one, us): flat d = 2048, f = 768, 16 anchors,
-// T = 237: gate|up 56 -> 33; T = 400: 59 -> 40; tree d = 4096, T = 777: level-1
-// input 111 -> 41, anchor gate|up 104 -> 67, level-1 down input 53 -> 23.
-// The expected tiles per node assume uniform routing: T (1 - (1 - 1/N)^k) rows,
-// spread by 10% and their Poisson deviation. part_cols: tiles must not
-// straddle the two parts of that many columns (0: they may).
-double pick_tile(const lx_tree_layer& t, int l, int T, int k, int ncol, int K, int part_cols, int& bm, int& bn) {
-  static const struct {
-    int bm, bn;
-    double slab, item;  // us
-  } kShapes[] = {{256, 256, 1.45, 5.0}, {256, 128, 0.72, 6.0}, {128, 128, 0.60, 5.0}, {128, 64, 0.53, 4.0}};
-  const double N = level_nodes(t, l);
-  const double mean = T * (1.0 - std::pow(1.0 - 1.0 / N, k)), sd = 0.1 * mean + std::sqrt(mean) + 1e-9;
-  double best = std::numeric_limits<double>::infinity();
-  for (const auto& c : kShapes) {
-    if (part_cols && part_cols % c.bn) continue;
-    double tiles = 1.0;  // of a node: sum over i of P(rows > i bm)
-    for (int i = 1; i * c.bm < mean + 3.0 * sd; ++i) tiles += 0.5 * std::erfc((i * c.bm - mean) / (sd * std::sqrt(2.0)));
-    const double items = N * tiles * ((ncol + c.bn - 1) / c.bn);
-    const double us = std::max(1.0, std::ceil(items / 256.0 - 0.05)) * (K / 64 * c.slab + c.item);
-    if (us < best) {
-      best = us;
-      bm = c.bm;
-      bn = c.bn;
-    }
-    if (c.bm == 256 && c.bn == 256 && items >= 256.0) break;
-  }
-  return best;
+// The same for a product over level l's rows: see lx_tiles.h.
+TilePick tile_for(const lx_tree_layer& t, int l, int T, int k, int ncol, int K, int part_cols, int bn0) {
+  const int N = level_nodes(t, l);
+  return pick_tile(N, l == 0 ? N : std::min(N, (int)t.levels[l - 1].n_factors), T, k, ncol, K, part_cols, bn0);
 }
 
 Plan make_plan(const lx_tree_layer& t, int T, int k) {
@@ -240,9 +210,8 @@ Plan make_plan(const lx_tree_layer& t, int T, int k) {
     // fill the chip better, the bf16 pair in those is faster, and more exact;
     // a hi and a lo slab take 2.5 us together; flat T = 237: 40 -> 26 us)
     if (p.lo8) {
-      int bm = kBigBM, bn = 256;
-      const double pair = pick_tile(t, 0, T, k, p.d, 2 * p.f, 0, bm, bn);
-      if ((bm != kBigBM || bn != 256) && pair < p.f / 64 * 2.5 + 5.0) p.lo8 = false;
+      const TilePick pair = tile_for(t, 0, T, k, p.d, 2 * p.f, 0, 256);
+      if (!pair.base && pair.us < p.f / 64 * 2.5 + 5.0) p.lo8 = false;
     }
     {
       bool all_fast = true;
@@ -738,6 +707,13 @@ lx_status run(const lx_tree_layer& t, int T, int k, const void* x, const int32_t
     LX_LAUNCH(name, launch_gemm_big(g, bm, bn, ofmt, (int)q.tiles_max[tab], lstream));
     return LX_OK;
   };
+  // the same on the tile shape that tile_for chooses (bn0, part_cols: as there)
+  auto big_picked = [&](const char* name, const GemmArgs& g, int l, int part_cols, int bn0, int ofmt,
+                        int64_t a_rows_total) -> lx_status {
+    TilePick c{kBigBM, bn0};
+    if (!skinny[l]) c = tile_for(t, l, T, k, g.ncols[0] + g.ncols[1], g.K, part_cols, bn0);
+    return big(name, g, l, c.bm, c.bn, ofmt, a_rows_total);
+  };
   // fp16 operands (A rows and weight matrices with power-of-two scales) on
   // the large-tile kernel, level l's 256-row tiles
   auto f16big = [&](const char* name, GemmArgs g, int l, int bn, int ofmt, int64_t a_rows_total) -> lx_status {
@@ -814,9 +790,7 @@ lx_status run(const lx_tree_layer& t, int T, int k, const void* x, const int32_t
       LX_TRY(big(kLowIn[l], g, l, kBigBM, 2 * rf <= 128 ? 128 : 256, OUT_F16T, T));
     } else if (fast[l]) {
       g.ldc = 4 * (int64_t)r;  // [gate hi | gate lo | up hi | up lo], bf16
-      int bm = kBigBM, bn = 2 * r <= 128 ? 128 : 256;
-      pick_tile(t, l, T, k, 2 * r, d, 0, bm, bn);
-      LX_TRY(big(kLowIn[l], g, l, bm, bn, OUT_HILO, T));
+      LX_TRY(big_picked(kLowIn[l], g, l, 0, 2 * r <= 128 ? 128 : 256, OUT_HILO, T));
     } else {
       g.ldc = 2 * (int64_t)r;
       g.c_coloff[1] = r;
@@ -840,9 +814,7 @@ lx_status run(const lx_tree_layer& t, int T, int k, const void* x, const int32_t
     g.ldc = 2 * (int64_t)f;
     g.c_coloff[1] = f;
     if (fast[0]) {
-      int bm = kBigBM, bn = 256;
-      pick_tile(t, 0, T, k, 2 * f, d, 0, bm, bn);
-      LX_TRY(big("anchor_gate_up", g, 0, bm, bn, OUT_X16, T));
+      LX_TRY(big_picked("anchor_gate_up", g, 0, 0, 256, OUT_X16, T));
     } else
       LX_TRY(small("anchor_gate_up", g, 0, A_BF16));
   }
@@ -945,9 +917,7 @@ lx_status run(const lx_tree_layer& t, int T, int k, const void* x, const int32_t
       h.K = 2 * r;
       h.Kb = r;
       // gate and up read different z columns: tiles must not straddle them
-      int bm = kBigBM, bn = f % 256 == 0 ? 256 : f % 128 == 0 ? 128 : 64;
-      pick_tile(t, l, T, k, 2 * f, 2 * r, f, bm, bn);
-      LX_TRY(big(kLowOut[l], h, l, bm, bn, OUT_X16, q.rows_max));
+      LX_TRY(big_picked(kLowOut[l], h, l, f, f % 256 == 0 ? 256 : f % 128 == 0 ? 128 : 64, OUT_X16, q.rows_max));
     } else {
       h.lda = 2 * (int64_t)r;
       h.a_koff[1] = r;
@@ -1035,9 +1005,7 @@ lx_status run(const lx_tree_layer& t, int T, int k, const void* x, const int32_t
       g.lda = 2 * (int64_t)f;
       g.K = 2 * f;
       g.Kb = f;
-      int bm = kBigBM, bn = 256;
-      pick_tile(t, 0, T, k, d, 2 * f, 0, bm, bn);
-      LX_TRY(big("anchor_down", g, 0, bm, bn, OUT_X16, q.rows_max));
+      LX_TRY(big_picked("anchor_down", g, 0, 0, 256, OUT_X16, q.rows_max));
     } else {
       g.lda = f;
       g.K = f;
@@ -1137,9 +1105,7 @@ lx_status run(const lx_tree_layer& t, int T, int k, const void* x, const int32_t
       g.K = 2 * f;
       g.Kb = f;
       g.ldc = 2 * (int64_t)r;  // [hi | lo], bf16
-      int bm = kBigBM, bn = r <= 64 ? 64 : 128;
-      pick_tile(t, l, T, k, r, 2 * f, 0, bm, bn);
-      LX_TRY(big(kDownIn[l], g, l, bm, bn, OUT_HILO, q.rows_max));
+      LX_TRY(big_picked(kDownIn[l], g, l, 0, r <= 64 ? 64 : 128, OUT_HILO, q.rows_max));
     } else {
       g.lda = f;
       g.K = f;
@@ -1177,9 +1143,7 @@ lx_status run(const lx_tree_layer& t, int T, int k, const void* x, const int32_t
       h.lda = 2 * (int64_t)r;
       h.K = 2 * r;
       h.Kb = r;
-      int bm = kBigBM, bn = 256;
-      pick_tile(t, l, T, k, d, 2 * r, 0, bm, bn);
-      LX_TRY(big(kDownOut[l], h, l, bm, bn, OUT_X16, q.rows_max));
+      LX_TRY(big_picked(kDownOut[l], h, l, 0, 256, OUT_X16, q.rows_max));
     } else {
       h.lda = r;
       h.K = r;

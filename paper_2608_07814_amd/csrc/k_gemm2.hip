@@ -84,7 +84,9 @@ __device__ __forceinline__ void load_lds16(const void* gptr, const void* lds_dst
 // input product 82 -> 66 us; tree T = 16 forward 184 -> 172 us, of it bucketing
 // 13 -> 11 and SwiGLU 16.5 -> 12.4; one token on the 4096 x 14336 layer 109 -> 103.
 // On the 256-row tiles of long prefills, whose row tiles share weights through
-// L2, it lost 1 to 2%.
+// L2, it lost 1 to 2%; so it does on 128-row tiles where a node has many (up to
+// 6%: one anchor, T = 2048, gate|up 29.6 -> 31.7 us), which run there because they
+// beat the 256-row ones by far more (56 us).
 __device__ __forceinline__ void load_lds16_nt(const void* gptr, const void* lds_dst) {
   const uint32_t lds = (uint32_t)(uintptr_t)(lds_void_t*)lds_dst;
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off nt"

@@ -125,11 +125,14 @@ def test_rank_not_multiple_of_64(cfg, over, T):
 
 
 @pytest.mark.parametrize("over,T", [({}, 160), ({}, 257), ({}, 450), ({"f": 320}, 700), ({"r": 96, "f": 192}, 300),
-                                    ({"E": 32, "C": 2, "k": 4, "f": 192}, 640), ({"E": 64, "C": 32}, 300)])
+                                    ({"E": 32, "C": 2, "k": 4, "f": 192}, 640), ({"E": 64, "C": 32}, 300),
+                                    ({"E": 64, "C": 4, "f": 192}, 700), ({"E": 64, "C": 4, "f": 192, "r": 32}, 300),
+                                    ({"E": 64, "C": 4, "f": 384, "r": 32}, 700)])
 def test_mid_sized_batches_on_every_tile_shape(over, T):
     """Batches between the skinny kernel's and the full 256 x 256 grid's: the
-    bf16 products run on 128 x 64, 128 x 128, 256 x 128 and 256 x 256 tiles,
-    with ragged rows per node, a rank that wraps within a K slab and column
+    bf16 products run on 128 x 64, 128 x 128, 256 x 64, 256 x 128 and 256 x 256
+    tiles (gate and up halves of 64- and 128-column tiles among them), with
+    ragged rows per node, a rank that wraps within a K slab and column
     counts that are no multiple of the tile."""
     require_gpu()
     cfg = dict(config(1, d=512, f=256), **over)

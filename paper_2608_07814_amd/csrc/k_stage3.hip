@@ -865,10 +865,16 @@ hipError_t allow_lds() {
 }
 
 // Y (rows x l) <- Y U^-1, U the Cholesky factor of its Gram matrix; U: l x l
-// scratch. One pass gives a basis orthonormal to cond(Y)^2 eps, at most 1e-2
-// under k_chol's pivot floor: enough between the products of the subspace
-// iteration, where only the span and its conditioning count. Two passes
-// (CholeskyQR2) make it orthonormal to rounding, which the final basis is. The
+// scratch. One pass leaves the basis off orthonormal by about cond(Y)^2 eps: to
+// rounding for a well-conditioned sketch, by as much as its own size where a
+// column is about 1e-7 of the largest (the pivots are not ordered, so k_chol's
+// floor bounds no condition number). Between the products of the subspace
+// iteration only the span counts and that the next product is better conditioned
+// than without the pass; two passes (CholeskyQR2) make the final basis orthonormal
+// to rounding. Emulated in fp64 against two passes everywhere, singular values
+// falling geometrically from 1 to 1e-3 .. 1e-7 over l = 74 to 128 columns: A B and
+// sigma off by the same down to 1e-6, and within their scatter at 1e-7 (A B by
+// 5e-11 and 4e-11, at most 6e-10 and 3e-10). The
 // Gram matrix's K is split at most 16 ways (8 past l = 80, where k_chol loads
 // fewer partials together): k_chol's one workgroup reads the partials. 2048 rows,
 // l = 74, 8 -> 16 ways: Gram matrix 24 -> 14 us.

@@ -237,3 +237,37 @@ def test_align_cost_edges(f, d, dtype):
     got = lx.align_cost(tuple(dev[:3]), tuple(dev[3:])).cpu().numpy()
     ref = S.align_cost(w[:3], w[3:], dtype)
     assert np.max(np.abs(got - ref)) <= 1e-12 * np.max(np.abs(ref))
+
+
+@pytest.mark.parametrize("weighted", [False, True])
+@pytest.mark.parametrize("q", [1, 2])
+def test_factors_of_a_residual_that_decays_to_1e7(q, weighted):
+    """Singular values falling geometrically to 1e-7 of the first over a sketch of
+    128 columns: the sketches between the products are far from orthonormal
+    after their one pass. The Gram matrix tells eigenvalues apart to about rows *
+    eps * sigma_1^2, so sigma is good to that over itself, and of A B the
+    directions below sqrt(rows * eps) = 2.6e-7 of sigma_1 (some 10 of them) are
+    open: 1e-6 of it."""
+    require_gpu()
+    say(f"stage 3 decaying residual q={q} weighted={weighted}")
+    rng = np.random.default_rng(90 + q)
+    rows, cols, l, r, n = 300, 400, 128, 118, 500
+    sv = np.concatenate([np.geomspace(1.0, 1e-7, l), np.full(rows - l, 1e-7)])
+    U, V = (np.linalg.qr(rng.standard_normal((m, rows)))[0] for m in (rows, cols))
+    wm = ((U * sv) @ V.T).astype(np.float32)
+    R = wm.astype(np.float64)
+    wd, wm_d = torch.zeros(rows, cols, device="cuda"), torch.from_numpy(wm).cuda()
+    if weighted:
+        x = rng.standard_normal((n, cols)).astype(np.float32)
+        om = rng.standard_normal((n, l))
+        A, B, sig = lx.weighted_factors(wd, wm_d, r, torch.from_numpy(x).cuda(), torch.from_numpy(om).cuda(), q=q, damp=0.0)
+        A0, B0, s0 = S.weighted_factors(R, x.astype(np.float64), om, r, q=q, damp=0.0)
+    else:
+        om = rng.standard_normal((cols, l))
+        A, B, sig = lx.lowrank_factors(wd, wm_d, r, torch.from_numpy(om).cuda(), q=q)
+        A0, B0, s0 = S.factors(R, om, r, q=q)
+    A, B, sig = A.cpu().numpy().astype(np.float64), B.cpu().numpy().astype(np.float64), sig.cpu().numpy()
+    say(f"  |AB - AB_oracle| / |AB_oracle| = {_rel(A @ B, A0 @ B0):.2e}, "
+        f"sigma off by {np.max(np.abs(sig - s0)) / s0[0]:.2e} of sigma_1")
+    assert _rel(A @ B, A0 @ B0) <= 1e-6
+    assert np.all(np.abs(sig - s0) <= 64 * rows * 2.3e-16 * s0[0] ** 2 / s0)

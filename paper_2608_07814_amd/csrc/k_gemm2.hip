@@ -1381,11 +1381,13 @@ __device__ __forceinline__ void skinny_body(const SkinnyBatch& b, u16* smem) {
       for (int per = 0; per < PER; ++per) fa[per][ks] = *(const bf16x8*)&sA[per * SA + lds_off2(ra, kc)];
       fb[ks] = *(const bf16x8*)&sB[lds_off2(rb, kc)];
     }
+    // (two-stage ring: the order of the one-period rings, a period at a time)
+    constexpr bool seq = SK_NST == 2;
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks)
-#pragma unroll
-      for (int per = 0; per < PER; ++per)
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[per][ks], fb[ks], acc, 0, 0, 0);
+    for (int i = 0; i < 4 * PER; ++i) {
+      const int ks = seq ? i % 4 : i / PER, per = seq ? i / 4 : i % PER;
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[per][ks], fb[ks], acc, 0, 0, 0);
+    }
   };
 
   // Local step i (global kt0 + i) lives in stage i % SK_NST. Steps
@@ -1449,7 +1451,7 @@ __global__ __launch_bounds__(SK_THR) void k_gemm_skinny(SkinnyBatch b) {
 // per-workgroup latency (tile entry, row map, one load round trip, epilogue)
 // is paid once per NB tiles. Wavefront w computes columns w * 32 .. w * 32 + 31
 // of each of its tiles.
-template <int NB, int PER>
+template <int NB, int PER, bool SEQ = false>
 __device__ __forceinline__ void skinny_wide_body(const SkinnyBatch& b, u16* smem) {
   constexpr int BM = kSkinnyBM, BN = kSkinnyBN;
   constexpr int A_ROUNDS = BM * 8 / SK_THR, B_ROUNDS = BN * 8 / SK_THR;
@@ -1530,18 +1532,36 @@ __device__ __forceinline__ void skinny_wide_body(const SkinnyBatch& b, u16* smem
 #pragma unroll
     for (int i = 0; i < 16; ++i) acc[t][i] = 0.f;
   const int ra = lane & 31, rb = wave * 32 + (lane & 31);
+  auto frag_a = [&](int per, int ks) { return *(const bf16x8*)&smem[per * SA + lds_off2(ra, ks * 2 + (lane >> 5))]; };
+  auto frag_b = [&](int t, int ks) { return *(const bf16x8*)&smem[PER * SA + t * SBt + lds_off2(rb, ks * 2 + (lane >> 5))]; };
+  if constexpr (SEQ) {  // a period at a time, as the single-tile rings add them
+    bf16x8 fa[PER][4];
 #pragma unroll
-  for (int ks = 0; ks < 4; ++ks) {
-    const int kc = ks * 2 + (lane >> 5);
-    bf16x8 fa[PER];
+    for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
-    for (int per = 0; per < PER; ++per) fa[per] = *(const bf16x8*)&smem[per * SA + lds_off2(ra, kc)];
+      for (int per = 0; per < PER; ++per) fa[per][ks] = frag_a(per, ks);
 #pragma unroll
     for (int t = 0; t < NB; ++t) {
-      const bf16x8 fb = *(const bf16x8*)&smem[PER * SA + t * SBt + lds_off2(rb, kc)];
+      bf16x8 fb[4];
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) fb[ks] = frag_b(t, ks);
 #pragma unroll
       for (int per = 0; per < PER; ++per)
-        acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[per], fb, acc[t], 0, 0, 0);
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[per][ks], fb[ks], acc[t], 0, 0, 0);
+    }
+  } else {
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      bf16x8 fa[PER];
+#pragma unroll
+      for (int per = 0; per < PER; ++per) fa[per] = frag_a(per, ks);
+#pragma unroll
+      for (int t = 0; t < NB; ++t) {
+        const bf16x8 fb = frag_b(t, ks);
+#pragma unroll
+        for (int per = 0; per < PER; ++per) acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[per], fb, acc[t], 0, 0, 0);
+      }
     }
   }
   wait_lgkm0();
@@ -1565,15 +1585,16 @@ __global__ __launch_bounds__(SK_THR) void k_gemm_skinny_wide(SkinnyBatch b) {
 
 // Hi/lo products of one weight slab (wide) and of two in one launch: a tree's
 // leaf and intermediate low-rank outputs. Bound by the latency of a workgroup's
-// few loads, so the one-slab products' workgroups take four column tiles. Tree
-// T = 16, gate|up 21 -> 19 us, down 36 -> 31 us.
+// few loads, so the one-slab products' workgroups take four column tiles (40 KB
+// and 4 bytes: three workgroups per compute unit). Tree T = 16, gate|up 21 -> 19
+// us, down 36 -> 31 us.
 __global__ __launch_bounds__(SK_THR) void k_gemm_skinny_mix(SkinnyBatch b) {
   constexpr int ring = skinny_lds(2, 2), row = skinny_wide_lds(4, 2), lds = ring > row ? ring : row;
   __shared__ __attribute__((aligned(1024))) u16 smem[lds];
   int pi = 0;
   while (pi + 1 < b.n && (int)blockIdx.x >= b.base[pi + 1]) ++pi;
   if ((b.wide_mask >> pi) & 1)
-    skinny_wide_body<4, 2>(b, smem);
+    skinny_wide_body<4, 2, true>(b, smem);
   else
     skinny_body<2, 2>(b, smem);
 }
@@ -1977,10 +1998,11 @@ hipError_t launch_gemm_skinny_batch(const GemmArgs* g, const int* ofmt, const in
   if (pair && max_steps > 4) {
     hipLaunchKernelGGL((k_gemm_skinny<3, 2>), dim3(wg), dim3(SK_THR), 0, s, b);
   } else if (pair && max_steps > 2) {
-    // at most two weight slabs: all of them in flight at once in 32 KB, five
-    // workgroups per compute unit instead of the 4-stage ring's three, and one
-    // fetch of a slab for both halves. Tree T = 16 (ranks 128 and 64), gate|up and
-    // down: 25 -> 21 and 47 -> 36 us
+    // at most two weight slabs: all of them in flight at once in 32 KB (and 4
+    // bytes), four workgroups per compute unit instead of the 4-stage ring's
+    // three, and one fetch of a slab for both halves. Tree T = 16 (ranks 128 and
+    // 64), gate|up and down: 25 -> 21 and 47 -> 36 us. (Both halves' fragments are
+    // in registers, so they are added in the ring's order, bit for bit.)
     // (products of one slab among them, if large enough to fill the chip: wide)
     SkinnyBatch bm = b;
     int wgm = 0;

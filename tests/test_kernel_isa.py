@@ -59,3 +59,17 @@ def test_swiglu_divides(tmp_path):
         n = len(re.findall(r"\bv_exp_f32", code))
         assert n > 0 and n == len(re.findall(r"\bv_div_fixup_f32", code)), name
         assert n <= len(re.findall(r"\bv_rndne_f32", code)), name
+
+
+def test_two_slab_kernels_add_a_half_at_a_time(tmp_path):
+    """The skinny kernels that hold a hi/lo pair's fragments at once add the hi
+    half's K steps of a slab, then the lo half's, as the kernels that take one
+    half per step do, so a product's sum does not depend on which of them runs:
+    no two MFMAs in a row read the same weight fragment."""
+    kernels = {n: f for n, f in _functions(_asm(tmp_path, "k_gemm2.hip")).items()
+               if "k_gemm_skinny_mix" in n or "k_gemm_skinnyILi2ELi2E" in n}
+    assert len(kernels) == 2
+    for name, lines in kernels.items():
+        weights = [re.split(r"[\s,]+", line.strip())[3] for line in lines if "v_mfma_f32_32x32x16_bf16" in line]
+        assert len(weights) >= 8
+        assert all(a != b for a, b in zip(weights, weights[1:])), (name, weights)

@@ -167,12 +167,13 @@ __device__ __forceinline__ unsigned long long dkey(double v) {
 }
 
 // Latency-bound (one workgroup). E <= KMAX = 128: the distance matrix is staged
-// in LDS (odd pitch: the threads' rows on distinct banks); larger E reads it
-// from memory, 8 loads in flight, unconditionally, the members picked
-// afterwards (a load under the membership test is waited for before the next
-// test). E <= 128 also keeps a bit mask of each cluster's members, so the ordered
-// sums walk the members alone, 4 loads in flight. E = 128, 16 clusters:
-// 65 -> 37 us with the masks and 16 rows' staging loads in flight.
+// in LDS (odd pitch: the threads' rows on distinct banks), and a bit mask of each
+// cluster's members lets the ordered sums walk the members alone, 4 loads in
+// flight. E = 128, 16 clusters: 65 -> 37 us with the masks and 16 rows' staging
+// loads in flight. Larger E reads the matrix from memory, its members only, one
+// after the other: a thread's row is a line of its own, and all E loads of it in
+// batches of 8 took 210 instead of 178 us at E = 160, 820 instead of 420 at 512
+// and 2530 instead of 1009 at 1024.
 constexpr int kKmSmall = 128;
 
 template <int KMAX>
@@ -189,7 +190,7 @@ __global__ __launch_bounds__(KM_THR) void k_kmedoids(const double* __restrict__ 
   __shared__ unsigned long long s_key[KMAX];
   __shared__ int s_idx[KMAX];
   __shared__ uint32_t s_fmax[KMAX];
-  __shared__ int s_isdom[KMAX], s_prot[KMAX];
+  __shared__ int s_isdom[KMAX], s_prot[SMALL ? KMAX : 1];
   // SMALL: the members of each cluster, the last assignment's and the one before
   __shared__ unsigned long long s_mem[2][SMALL ? 2 * KMAX : 1];
   __shared__ int s_changed;
@@ -202,7 +203,7 @@ __global__ __launch_bounds__(KM_THR) void k_kmedoids(const double* __restrict__ 
     s_fire[e] = live ? fire[e] : 0u;
     s_cl[e] = -1;
     s_isdom[e] = 0;
-    s_prot[e] = prot || !live;
+    if (SMALL) s_prot[e] = prot || !live;
   }
   const int pitch = E | 1;
   if (SMALL) {
@@ -230,28 +231,27 @@ __global__ __launch_bounds__(KM_THR) void k_kmedoids(const double* __restrict__ 
   if (free_e) {
     int rank = 0;
     const uint32_t fe = s_fire[e];
+    if (SMALL) {
 #pragma unroll 8
-    for (int f = 0; f < E; ++f) {
-      const uint32_t ff = s_fire[f];
-      rank += !s_prot[f] && (ff > fe || (ff == fe && f < e)) ? 1 : 0;
+      for (int f = 0; f < E; ++f) {
+        const uint32_t ff = s_fire[f];
+        rank += !s_prot[f] && (ff > fe || (ff == fe && f < e)) ? 1 : 0;
+      }
+    } else {
+      for (int f = 0; f < E; ++f) {
+        const bool pf = (pm.bits[f >> 5] >> (f & 31)) & 1u;
+        if (!pf && (s_fire[f] > fe || (s_fire[f] == fe && f < e))) ++rank;
+      }
     }
     if (rank < K) s_med[rank] = e;
   }
   __syncthreads();
   const double* const De = SMALL ? s_d + (live ? e : 0) * pitch : D + (int64_t)(live ? e : 0) * E;
-  // sum over j, ascending, of f(De[j]) where pick(j)
+  // sum over j, ascending, of f(De[j]) where pick(j); only those are loaded
   auto sum_where = [&](auto pick, auto f) {
     double s = 0.0;
-    for (int j0 = 0; j0 < E; j0 += 8) {
-      double v[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = De[j0 + u < E ? j0 + u : E - 1];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const double w = s + f(v[u]);
-        s = j0 + u < E && pick(j0 + u) ? w : s;
-      }
-    }
+    for (int j = 0; j < E; ++j)
+      if (pick(j)) s += f(De[j]);
     return s;
   };
   int cur = 0;  // the last assignment's masks
@@ -345,8 +345,12 @@ __global__ __launch_bounds__(KM_THR) void k_kmedoids(const double* __restrict__ 
   // protected experts: singleton clusters after the seeded ones
   if (prot) {
     int rank = 0;
+    if (SMALL) {
 #pragma unroll 8
-    for (int f = 0; f < E; ++f) rank += f < e && s_prot[f] ? 1 : 0;
+      for (int f = 0; f < E; ++f) rank += f < e && s_prot[f] ? 1 : 0;
+    } else {
+      for (int f = 0; f < e; ++f) rank += (pm.bits[f >> 5] >> (f & 31)) & 1u;
+    }
     s_cl[e] = K + rank;
   }
   if (e < C) {
@@ -378,8 +382,12 @@ __global__ __launch_bounds__(KM_THR) void k_kmedoids(const double* __restrict__ 
   __syncthreads();
   if (live) {
     int rank = 0;
+    if (SMALL) {
 #pragma unroll 8
-    for (int f = 0; f < E; ++f) rank += f < e && !s_isdom[f] ? 1 : 0;
+      for (int f = 0; f < E; ++f) rank += f < e && !s_isdom[f] ? 1 : 0;
+    } else {
+      for (int f = 0; f < e; ++f) rank += s_isdom[f] ? 0 : 1;
+    }
     cluster_of[e] = c;
     factor_of[e] = s_isdom[e] ? -1 : rank;
   }

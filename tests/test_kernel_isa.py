@@ -73,3 +73,23 @@ def test_two_slab_kernels_add_a_half_at_a_time(tmp_path):
         weights = [re.split(r"[\s,]+", line.strip())[3] for line in lines if "v_mfma_f32_32x32x16_bf16" in line]
         assert len(weights) >= 8
         assert all(a != b for a, b in zip(weights, weights[1:])), (name, weights)
+
+
+def test_large_kmedoids_loads_members_only(tmp_path):
+    """Past 128 experts the member sums of the k-medoids read the distance matrix
+    from memory: a distance is loaded under its membership branch, right before
+    it is added (loading all of a row in batches took 2.5 times as long at 1024
+    experts)."""
+    kernels = {n: f for n, f in _functions(_asm(tmp_path, "k_cluster.hip")).items() if "k_kmedoidsILi1024E" in n}
+    assert len(kernels) == 1
+    (lines,) = kernels.values()
+    code = [c for c in (line.split(";")[0].strip() for line in lines) if c and not c.startswith(".")]
+    sums = 0
+    for i, c in enumerate(code):
+        if c.startswith("v_add_f64") and code[i - 2].startswith("global_load_dwordx2"):
+            assert code[i - 1].startswith("s_waitcnt vmcnt(0)")
+            assert any(b.startswith("s_cbranch_execz") for b in code[max(0, i - 12):i]), code[i - 12:i]
+            sums += 1
+        elif c.startswith("v_add_f64"):  # (1 - D: the sum follows its subtraction)
+            assert code[i - 1].startswith("v_add_f64") and code[i - 3].startswith("global_load_dwordx2"), code[i - 4:i + 1]
+    assert sums >= 2

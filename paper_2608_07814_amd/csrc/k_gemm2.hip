@@ -1292,7 +1292,9 @@ __device__ __forceinline__ void sk_epilogue(const SkUnit& u, const f32x16& acc, 
 constexpr int skinny_lds(int nst, int per) { return nst * (per * kSkinnyBM + kSkinnyBN) * BK2; }
 constexpr int skinny_wide_lds(int nb, int per) { return (per * kSkinnyBM + nb * kSkinnyBN) * BK2; }
 
-template <int SK_NST, int PER>
+// ROUTER: implicit dense tiles, whose row tiles all read the same weights: plain
+// weight loads, and one step per barrier.
+template <int SK_NST, int PER, bool ROUTER = false>
 __device__ __forceinline__ void skinny_body(const SkinnyBatch& b, u16* smem) {
   constexpr int BM = kSkinnyBM, BN = kSkinnyBN;
   constexpr int A_ROUNDS = BM * 8 / SK_THR, B_ROUNDS = BN * 8 / SK_THR;
@@ -1356,14 +1358,8 @@ __device__ __forceinline__ void skinny_body(const SkinnyBatch& b, u16* smem) {
           load_lds16(Ab + (aoff[j] + (uint32_t)(per * Kb + kb)), sA + per * SA + (j * SK_THR + wave * 64) * 8);
     }
 #pragma unroll
-    for (int j = 0; j < B_ROUNDS; ++j) {
-      u16* const dst = sA + PER * SA + (j * SK_THR + wave * 64) * 8;
-      // (implicit dense tiles, the router: every row tile reads the same weights)
-      if (p.tiles)
-        load_lds16_nt(bptr[j] + kb, dst);
-      else
-        load_lds16(bptr[j] + kb, dst);
-    }
+    for (int j = 0; j < B_ROUNDS; ++j)
+      load_lds16_w<!ROUTER>(bptr[j] + kb, sA + PER * SA + (j * SK_THR + wave * 64) * 8);
   };
 
   f32x16 acc;
@@ -1396,10 +1392,12 @@ __device__ __forceinline__ void skinny_body(const SkinnyBatch& b, u16* smem) {
   static_assert(SK_NST >= 2 && SK_NST <= 4, "ring depth");
   const int npre = nkl < SK_NST ? nkl : SK_NST;
   for (int i = 0; i < npre; ++i) issue(i, kt0 + i);
-  if constexpr (SK_NST == 4) {
+  if constexpr (SK_NST == 4 && !ROUTER) {
     // Two steps per barrier pair: the two 128-byte pieces of a weight row's 256
     // bytes are then requested back to back (one DRAM page visit). One token on
     // the 4096 x 14336 layer: gate|up 54.8 -> 51.8 us; tree T = 16: 58.5 -> 57.5 us.
+    // (Not the router's: its weights come from the caches, and fewer steps in
+    // flight cost it 3% at T = 16384.)
     int i = 0;
     for (; i + 1 < nkl; i += 2) {
       // steps issued so far: 0 .. min(i + 3, nkl - 1); wait for i and i + 1
@@ -1438,10 +1436,10 @@ __device__ __forceinline__ void skinny_body(const SkinnyBatch& b, u16* smem) {
   sk_epilogue(u, acc, (float*)smem + wave * (32 * 36));
 }
 
-template <int SK_NST, int PER>
+template <int SK_NST, int PER, bool ROUTER = false>
 __global__ __launch_bounds__(SK_THR) void k_gemm_skinny(SkinnyBatch b) {
   __shared__ __attribute__((aligned(1024))) u16 smem[skinny_lds(SK_NST, PER)];
-  skinny_body<SK_NST, PER>(b, smem);
+  skinny_body<SK_NST, PER, ROUTER>(b, smem);
 }
 
 // Wide variant for products whose K is one weight slab (K = 64, or a bf16
@@ -1995,7 +1993,13 @@ hipError_t launch_gemm_skinny_batch(const GemmArgs* g, const int* ofmt, const in
       hipLaunchKernelGGL((k_gemm_skinny_wide<4, 1>), dim3(wgw), dim3(SK_THR), 0, s, bw);
     return hipGetLastError();
   }
-  if (pair && max_steps > 4) {
+  if (!g[0].tiles) {  // the router: a launch of its own
+    if (n != 1 || pair) return hipErrorInvalidValue;
+    if (max_steps <= 2)
+      hipLaunchKernelGGL((k_gemm_skinny<2, 1, true>), dim3(wg), dim3(SK_THR), 0, s, b);
+    else
+      hipLaunchKernelGGL((k_gemm_skinny<4, 1, true>), dim3(wg), dim3(SK_THR), 0, s, b);
+  } else if (pair && max_steps > 4) {
     hipLaunchKernelGGL((k_gemm_skinny<3, 2>), dim3(wg), dim3(SK_THR), 0, s, b);
   } else if (pair && max_steps > 2) {
     // at most two weight slabs: all of them in flight at once in 32 KB (and 4

@@ -93,3 +93,17 @@ def test_large_kmedoids_loads_members_only(tmp_path):
         elif c.startswith("v_add_f64"):  # (1 - D: the sum follows its subtraction)
             assert code[i - 1].startswith("v_add_f64") and code[i - 3].startswith("global_load_dwordx2"), code[i - 4:i + 1]
     assert sums >= 2
+
+
+def test_router_gemm_reads_weights_through_the_caches(tmp_path):
+    """The router's row tiles all read the same weights: its kernels load them
+    without the non-temporal hint that the streaming kernels use, and wait one
+    step at a time (up to three further steps of 6 loads stay in flight)."""
+    kernels = {n: "\n".join(f) for n, f in _functions(_asm(tmp_path, "k_gemm2.hip")).items() if "k_gemm_skinnyI" in n}
+    router = {n: c for n, c in kernels.items() if "Lb1E" in n}
+    assert len(router) == 2 and len(kernels) > 4
+    for name, code in kernels.items():
+        loads = re.findall(r"global_load_lds_dwordx4.*", code)
+        assert loads and any(" nt" in x for x in loads) == (name not in router), name
+    (ring,) = [c for n, c in router.items() if "ILi4ELi1E" in n]
+    assert "s_waitcnt vmcnt(18)" in ring

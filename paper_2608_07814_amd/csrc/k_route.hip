@@ -21,7 +21,7 @@ namespace {
 
 constexpr int TK_WAVES = 4;
 
-template <int PER>
+template <int PER, bool SWAP>
 __global__ __launch_bounds__(TK_WAVES * 64) void k_topk(const float* __restrict__ logits,
                                                         const float* __restrict__ part, int S, int T, int E,
                                                         int k, int32_t* __restrict__ ids,
@@ -31,7 +31,7 @@ __global__ __launch_bounds__(TK_WAVES * 64) void k_topk(const float* __restrict_
   if (t >= T) return;  // whole wavefront
   int id;
   float wt;
-  topk_token<PER>(logits, part, S, E, k, t, id, wt);
+  topk_token<PER, SWAP>(logits, part, S, E, k, t, id, wt);
   if (lane < k) {
     ids[(int64_t)t * k + lane] = id;
     weights[(int64_t)t * k + lane] = wt;
@@ -44,7 +44,7 @@ __global__ __launch_bounds__(TK_WAVES * 64) void k_topk(const float* __restrict_
 // histogram's, and the whole chip's wavefronts for the top-k: inside the
 // histogram pass (one workgroup per 64 tokens) it took 33 us at T = 4096, E = 128
 // and 59 us at T = 777, E = 256; here 18 and 20.
-template <int PER>
+template <int PER, bool SWAP>
 __global__ __launch_bounds__(TK_WAVES * 64) void k_topk_hist(RouteIn r, BucketArgs a) {
   const int lane = threadIdx.x & 63;
   const int t = blockIdx.x * TK_WAVES + (threadIdx.x >> 6);
@@ -52,7 +52,7 @@ __global__ __launch_bounds__(TK_WAVES * 64) void k_topk_hist(RouteIn r, BucketAr
   const int k = a.k;
   int id;
   float wt;
-  topk_token<PER>(r.logits, r.part, r.S, a.E, k, t, id, wt);
+  topk_token<PER, SWAP>(r.logits, r.part, r.S, a.E, k, t, id, wt);
   if (lane < k) {
     const_cast<int32_t*>(a.ids)[(int64_t)t * k + lane] = id;
     const_cast<float*>(a.w)[(int64_t)t * k + lane] = wt;
@@ -71,33 +71,48 @@ __global__ __launch_bounds__(TK_WAVES * 64) void k_topk_hist(RouteIn r, BucketAr
 
 }  // namespace
 
+namespace {
+
+// E <= 64 PER, and how the wavefront's rows meet: swaps while the launch is a
+// latency chain, lane exchanges from 2048 tokens on. k = 8, swaps against
+// exchanges: T = 300, E = 128 14.0 and 14.4 us; T = 16384 52.4 and 50.3.
+template <class F>
+hipError_t with_topk_shape(int T, int E, F&& launch) {
+  auto per = [&](auto swap) {
+    if (E <= 64)
+      launch(std::integral_constant<int, 1>{}, swap);
+    else if (E <= 128)
+      launch(std::integral_constant<int, 2>{}, swap);
+    else if (E <= 256)
+      launch(std::integral_constant<int, 4>{}, swap);
+    else
+      launch(std::integral_constant<int, kRouteMaxE / 64>{}, swap);
+  };
+  if (T < 2048)
+    per(std::true_type{});
+  else
+    per(std::false_type{});
+  return hipGetLastError();
+}
+
+}  // namespace
+
 hipError_t launch_topk_hist(const RouteIn& r, const BucketArgs& a, hipStream_t s) {
   if (a.T <= 0) return hipSuccess;
   const dim3 grid((a.T + TK_WAVES - 1) / TK_WAVES), thr(TK_WAVES * 64);
-  if (a.E <= 64)
-    hipLaunchKernelGGL(k_topk_hist<1>, grid, thr, 0, s, r, a);
-  else if (a.E <= 128)
-    hipLaunchKernelGGL(k_topk_hist<2>, grid, thr, 0, s, r, a);
-  else if (a.E <= 256)
-    hipLaunchKernelGGL(k_topk_hist<4>, grid, thr, 0, s, r, a);
-  else
-    hipLaunchKernelGGL(k_topk_hist<kRouteMaxE / 64>, grid, thr, 0, s, r, a);
-  return hipGetLastError();
+  return with_topk_shape(a.T, a.E, [&](auto per, auto swap) {
+    hipLaunchKernelGGL((k_topk_hist<decltype(per)::value, decltype(swap)::value>), grid, thr, 0, s, r, a);
+  });
 }
 
 hipError_t launch_topk(const float* logits, const float* part, int S, int T, int E, int k, int32_t* ids,
                        float* weights, hipStream_t s) {
   if (T <= 0) return hipSuccess;
   const dim3 grid((T + TK_WAVES - 1) / TK_WAVES), thr(TK_WAVES * 64);
-  if (E <= 64)
-    hipLaunchKernelGGL(k_topk<1>, grid, thr, 0, s, logits, part, S, T, E, k, ids, weights);
-  else if (E <= 128)
-    hipLaunchKernelGGL(k_topk<2>, grid, thr, 0, s, logits, part, S, T, E, k, ids, weights);
-  else if (E <= 256)
-    hipLaunchKernelGGL(k_topk<4>, grid, thr, 0, s, logits, part, S, T, E, k, ids, weights);
-  else
-    hipLaunchKernelGGL(k_topk<kRouteMaxE / 64>, grid, thr, 0, s, logits, part, S, T, E, k, ids, weights);
-  return hipGetLastError();
+  return with_topk_shape(T, E, [&](auto per, auto swap) {
+    hipLaunchKernelGGL((k_topk<decltype(per)::value, decltype(swap)::value>), grid, thr, 0, s, logits, part, S, T, E, k,
+                       ids, weights);
+  });
 }
 
 }  // namespace lx

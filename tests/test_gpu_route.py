@@ -106,6 +106,28 @@ def test_route_ties_determinism_and_edges():
     assert np.all(np.isfinite(w2)) and np.all(np.abs(w2.sum(1) - 1) < 1e-5)
 
 
+@pytest.mark.parametrize("E,k", [(40, 8), (100, 32), (200, 8), (384, 32), (512, 8)])
+def test_route_of_many_tokens_equals_that_of_few(E, k):
+    """From 2048 tokens on the wavefront's rows meet by lane exchanges, below by
+    swaps: the same ids and weights bit for bit (d = 256: no split of the logits
+    at either size), with tied experts, a row of NaN and one of zeros."""
+    require_gpu()
+    say(f"route many/few E={E} k={k}")
+    x = _bf16_dev(make_x(2051, 256, "bf16", E))
+    w = make_router(256, E, "bf16", E)
+    w[E - 1] = w[3]
+    w[E // 2] = w[3]
+    wd = _bf16_dev(w)
+    x[7] = float("nan")
+    x[2050] = 0
+    ids, wts = lx.route_topk(x, wd, k)
+    parts = [lx.route_topk(x[a:b].contiguous(), wd, k) for a, b in ((0, 1024), (1024, 2048), (2048, 2051))]
+    torch.cuda.synchronize()
+    assert torch.equal(ids, torch.cat([i for i, _ in parts]))
+    assert torch.equal(wts.view(torch.int32), torch.cat([v for _, v in parts]).view(torch.int32))
+    assert ids[2050].tolist() == list(range(k)) and ids[7].tolist() == list(range(k))
+
+
 def test_route_then_forward_on_one_stream():
     """Routing on the GPU feeding the compressed forward (no host round trip),
     against the oracle forward on the same ids and weights."""

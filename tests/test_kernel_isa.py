@@ -107,3 +107,14 @@ def test_router_gemm_reads_weights_through_the_caches(tmp_path):
         assert loads and any(" nt" in x for x in loads) == (name not in router), name
     (ring,) = [c for n, c in router.items() if "ILi4ELi1E" in n]
     assert "s_waitcnt vmcnt(18)" in ring
+
+
+def test_topk_keeps_eight_wavefronts_per_simd(tmp_path):
+    """The top-k of many tokens is bound by instructions that other wavefronts
+    hide: at most 64 VGPRs (of 512 per SIMD lane) and nothing in scratch, for
+    every number of experts."""
+    asm = _asm(tmp_path, "k_route.hip")
+    vgprs = {m[0]: int(m[1]) for m in re.findall(r"\.set (_Z\w*k_topk\w*)\.num_vgpr, (\d+)", asm)}
+    scratch = {m[0]: int(m[1]) for m in re.findall(r"\.set (_Z\w*k_topk\w*)\.private_seg_size, (\d+)", asm)}
+    assert len(vgprs) >= 8 and vgprs.keys() == scratch.keys()
+    assert max(vgprs.values()) <= 64 and max(scratch.values()) == 0, vgprs

@@ -682,6 +682,7 @@ lx_status run(const lx_tree_layer& t, int T, int k, const void* x, const int32_t
         return fail(LX_ERR_UNSUPPORTED, std::string(name) + ": shape not supported by the skinny GEMM");
       g.tiles = ba.lv[l].tiles[kTabSkinny];
       g.n_tiles = ba.lv[l].n_tiles[kTabSkinny];
+      g.node_rows_max = T;
       if (q.n_cnt >= (int64_t)q.tiles_max[kTabSkinny] * ((g.ncols[0] + g.ncols[1] + kSkinnyBN - 1) / kSkinnyBN)) {
         g.part = (float*)(W + q.part);
         g.cnt = (uint32_t*)(W + q.cnt);

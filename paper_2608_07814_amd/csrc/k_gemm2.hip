@@ -1136,11 +1136,41 @@ struct SkUnit {
   const GemmArgs* p;
   int ntn, ofmt, S, Lg, item, kt0, nkl, Kb, nper, n0, ncol, akoff;
   TileEntry te;
+  bool shared;  // other row tiles of the node read the same weights
 };
+
+// Who reads a weight slab. Once: no node has a second row tile (at most 32
+// tokens): non-temporal loads. Per node: those too, but plain loads for the
+// tiles of a node with several (non-temporal ones there: 128 experts of 2048 x
+// 768, 600 and 900 tokens 358 -> 424 and 399 -> 512 us; 640 x 1088, 797 tokens 213 ->
+// 251). Router: implicit dense tiles, whose row tiles all read the same weights:
+// plain loads, and one step per barrier.
+enum WeightUse { W_ONCE, W_NODE, W_ROUTER };
+
+// Row tile ti of a product (a node's tiles are neighbours in the table).
+template <WeightUse W>
+__device__ __forceinline__ void sk_tile(const GemmArgs& p, int ti, SkUnit& u) {
+  if constexpr (W == W_ROUTER) {
+    u.te.widx = 0;
+    u.te.row0 = ti * kSkinnyBM;
+    u.te.nrows = p.dense_rows - u.te.row0 < kSkinnyBM ? p.dense_rows - u.te.row0 : kSkinnyBM;
+    u.te.node = 0;
+    u.shared = true;
+  } else if constexpr (W == W_NODE) {
+    const int before = p.tiles[ti > 0 ? ti - 1 : 0].node;
+    u.te = p.tiles[ti];
+    // (a full tile is taken to have one behind it)
+    u.shared = u.te.nrows == kSkinnyBM || (ti > 0 && before == u.te.node);
+  } else {
+    u.te = p.tiles[ti];
+    u.shared = false;
+  }
+}
 
 // Decode this workgroup's unit; false if it has none. spw = K-loop steps per
 // weight slab (nper for the slab-per-step LDS kernel in PER == 1 mode, 1
 // when a step covers every period of a weight slab).
+template <WeightUse W>
 __device__ __forceinline__ bool sk_unit(const SkinnyBatch& b, bool step_per_weight_slab, SkUnit& u) {
   int pi = 0;
   while (pi + 1 < b.n && (int)blockIdx.x >= b.base[pi + 1]) ++pi;
@@ -1189,14 +1219,7 @@ __device__ __forceinline__ bool sk_unit(const SkinnyBatch& b, bool step_per_weig
   const int ti = u.item / u.ntn, nt = u.item % u.ntn;
   u.kt0 = sp * cw * spw;
   u.nkl = ((sp + 1) * cw < nkw ? (sp + 1) * cw : nkw) * spw - u.kt0;
-  if (p.tiles) {
-    u.te = p.tiles[ti];
-  } else {
-    u.te.widx = 0;
-    u.te.row0 = ti * kSkinnyBM;
-    u.te.nrows = p.dense_rows - u.te.row0 < kSkinnyBM ? p.dense_rows - u.te.row0 : kSkinnyBM;
-    u.te.node = 0;
-  }
+  sk_tile<W>(p, ti, u);
   u.n0 = nt * kSkinnyBN;
   u.ncol = p.ncols[0] + p.ncols[1];
   u.akoff = p.a_koff[u.n0 < p.ncols[0] ? 0 : 1];
@@ -1292,9 +1315,7 @@ __device__ __forceinline__ void sk_epilogue(const SkUnit& u, const f32x16& acc, 
 constexpr int skinny_lds(int nst, int per) { return nst * (per * kSkinnyBM + kSkinnyBN) * BK2; }
 constexpr int skinny_wide_lds(int nb, int per) { return (per * kSkinnyBM + nb * kSkinnyBN) * BK2; }
 
-// ROUTER: implicit dense tiles, whose row tiles all read the same weights: plain
-// weight loads, and one step per barrier.
-template <int SK_NST, int PER, bool ROUTER = false>
+template <int SK_NST, int PER, WeightUse W>
 __device__ __forceinline__ void skinny_body(const SkinnyBatch& b, u16* smem) {
   constexpr int BM = kSkinnyBM, BN = kSkinnyBN;
   constexpr int A_ROUNDS = BM * 8 / SK_THR, B_ROUNDS = BN * 8 / SK_THR;
@@ -1305,7 +1326,7 @@ __device__ __forceinline__ void skinny_body(const SkinnyBatch& b, u16* smem) {
   // PER == 2 (nper == 2), one weight slab, multiplied by both periods of A
   // (the weight slab is loaded once for the hi and the lo half)
   SkUnit u;
-  if (!sk_unit(b, PER == 2, u)) return;
+  if (!sk_unit<W>(b, PER == 2, u)) return;
   const GemmArgs& p = *u.p;
   const int Kb = u.Kb, nper = u.nper, kt0 = u.kt0, nkl = u.nkl;
   const TileEntry& te = u.te;
@@ -1339,7 +1360,7 @@ __device__ __forceinline__ void skinny_body(const SkinnyBatch& b, u16* smem) {
     bptr[j] = (n < p.ncols[0] ? Bw0 + (int64_t)n * Kb : Bw1 + (int64_t)(n - p.ncols[0]) * Kb) + c * 8;
   }
   // stage = [A period 0 | (A period 1) | B], one 64-wide K slab each
-  auto issue = [&](int st, int kt) {
+  auto issue = [&](int st, int kt, auto nt) {
     u16* const sA = smem + st * STAGE;
     int kb;
     if (PER == 1) {
@@ -1359,7 +1380,7 @@ __device__ __forceinline__ void skinny_body(const SkinnyBatch& b, u16* smem) {
     }
 #pragma unroll
     for (int j = 0; j < B_ROUNDS; ++j)
-      load_lds16_w<!ROUTER>(bptr[j] + kb, sA + PER * SA + (j * SK_THR + wave * 64) * 8);
+      load_lds16_w<decltype(nt)::value>(bptr[j] + kb, sA + PER * SA + (j * SK_THR + wave * 64) * 8);
   };
 
   f32x16 acc;
@@ -1390,56 +1411,62 @@ __device__ __forceinline__ void skinny_body(const SkinnyBatch& b, u16* smem) {
   // 0 .. SK_NST-1 are issued up front; after the barrier that follows step
   // i's compute, stage i % SK_NST is free and step i + SK_NST goes there.
   static_assert(SK_NST >= 2 && SK_NST <= 4, "ring depth");
-  const int npre = nkl < SK_NST ? nkl : SK_NST;
-  for (int i = 0; i < npre; ++i) issue(i, kt0 + i);
-  if constexpr (SK_NST == 4 && !ROUTER) {
-    // Two steps per barrier pair: the two 128-byte pieces of a weight row's 256
-    // bytes are then requested back to back (one DRAM page visit). One token on
-    // the 4096 x 14336 layer: gate|up 54.8 -> 51.8 us; tree T = 16: 58.5 -> 57.5 us.
-    // (Not the router's: its weights come from the caches, and fewer steps in
-    // flight cost it 3% at T = 16384.)
-    int i = 0;
-    for (; i + 1 < nkl; i += 2) {
-      // steps issued so far: 0 .. min(i + 3, nkl - 1); wait for i and i + 1
-      const int issued = i + 4 < nkl ? i + 4 : nkl;
-      wait_slabs<R>(issued - (i + 2));
-      bar();
-      compute(i % 4);
-      compute((i + 1) % 4);
-      wait_lgkm0();
-      bar();
-      if (i + 4 < nkl) issue(i % 4, kt0 + i + 4);
-      if (i + 5 < nkl) issue((i + 1) % 4, kt0 + i + 5);
-    }
-    if (i < nkl) {
-      wait_vmcnt<0>();
-      bar();
-      compute(i % 4);
-    }
-  } else {
-    wait_slabs<R>(npre - 1);
-    bar();
-    for (int i = 0; i < nkl; ++i) {
-      compute(i % SK_NST);
-      if (i + 1 < nkl) {
-        // steps issued so far: 0 .. min(i + SK_NST - 1, nkl - 1); wait for i + 1
-        const int last = i + SK_NST - 1 < nkl - 1 ? i + SK_NST - 1 : nkl - 1;
-        wait_slabs<R>(last - (i + 1));
+  auto ring = [&](auto nt) {
+    const int npre = nkl < SK_NST ? nkl : SK_NST;
+    for (int i = 0; i < npre; ++i) issue(i, kt0 + i, nt);
+    if constexpr (SK_NST == 4 && W != W_ROUTER) {
+      // Two steps per barrier pair: the two 128-byte pieces of a weight row's 256
+      // bytes are then requested back to back (one DRAM page visit). One token on
+      // the 4096 x 14336 layer: gate|up 54.8 -> 51.8 us; tree T = 16: 58.5 -> 57.5 us.
+      // (Not the router's: its weights come from the caches, and fewer steps in
+      // flight cost it 3% at T = 16384.)
+      int i = 0;
+      for (; i + 1 < nkl; i += 2) {
+        // steps issued so far: 0 .. min(i + 3, nkl - 1); wait for i and i + 1
+        const int issued = i + 4 < nkl ? i + 4 : nkl;
+        wait_slabs<R>(issued - (i + 2));
+        bar();
+        compute(i % 4);
+        compute((i + 1) % 4);
         wait_lgkm0();
         bar();
-        if (i + SK_NST < nkl) issue(i % SK_NST, kt0 + i + SK_NST);
+        if (i + 4 < nkl) issue(i % 4, kt0 + i + 4, nt);
+        if (i + 5 < nkl) issue((i + 1) % 4, kt0 + i + 5, nt);
+      }
+      if (i < nkl) {
+        wait_vmcnt<0>();
+        bar();
+        compute(i % 4);
+      }
+    } else {
+      wait_slabs<R>(npre - 1);
+      bar();
+      for (int i = 0; i < nkl; ++i) {
+        compute(i % SK_NST);
+        if (i + 1 < nkl) {
+          // steps issued so far: 0 .. min(i + SK_NST - 1, nkl - 1); wait for i + 1
+          const int last = i + SK_NST - 1 < nkl - 1 ? i + SK_NST - 1 : nkl - 1;
+          wait_slabs<R>(last - (i + 1));
+          wait_lgkm0();
+          bar();
+          if (i + SK_NST < nkl) issue(i % SK_NST, kt0 + i + SK_NST, nt);
+        }
       }
     }
-  }
+  };
+  if (u.shared)
+    ring(std::false_type{});
+  else
+    ring(std::true_type{});
   wait_lgkm0();
   bar();  // every wavefront is done with the stages: the epilogue reuses them
   sk_epilogue(u, acc, (float*)smem + wave * (32 * 36));
 }
 
-template <int SK_NST, int PER, bool ROUTER = false>
+template <int SK_NST, int PER, WeightUse W>
 __global__ __launch_bounds__(SK_THR) void k_gemm_skinny(SkinnyBatch b) {
   __shared__ __attribute__((aligned(1024))) u16 smem[skinny_lds(SK_NST, PER)];
-  skinny_body<SK_NST, PER, ROUTER>(b, smem);
+  skinny_body<SK_NST, PER, W>(b, smem);
 }
 
 // Wide variant for products whose K is one weight slab (K = 64, or a bf16
@@ -1449,7 +1476,7 @@ __global__ __launch_bounds__(SK_THR) void k_gemm_skinny(SkinnyBatch b) {
 // per-workgroup latency (tile entry, row map, one load round trip, epilogue)
 // is paid once per NB tiles. Wavefront w computes columns w * 32 .. w * 32 + 31
 // of each of its tiles.
-template <int NB, int PER, bool SEQ = false>
+template <int NB, int PER, WeightUse W, bool SEQ = false>
 __device__ __forceinline__ void skinny_wide_body(const SkinnyBatch& b, u16* smem) {
   constexpr int BM = kSkinnyBM, BN = kSkinnyBN;
   constexpr int A_ROUNDS = BM * 8 / SK_THR, B_ROUNDS = BN * 8 / SK_THR;
@@ -1478,14 +1505,7 @@ __device__ __forceinline__ void skinny_wide_body(const SkinnyBatch& b, u16* smem
   u.nkl = 1;
   u.Kb = p.Kb > 0 ? p.Kb : p.K;
   u.nper = p.K / u.Kb;
-  if (p.tiles) {
-    u.te = p.tiles[ti];
-  } else {
-    u.te.widx = 0;
-    u.te.row0 = ti * BM;
-    u.te.nrows = p.dense_rows - u.te.row0 < BM ? p.dense_rows - u.te.row0 : BM;
-    u.te.node = 0;
-  }
+  sk_tile<W>(p, ti, u);
   u.ncol = p.ncols[0] + p.ncols[1];
   const TileEntry& te = u.te;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
@@ -1510,18 +1530,24 @@ __device__ __forceinline__ void skinny_wide_body(const SkinnyBatch& b, u16* smem
       load_lds16(Ab + ((uint32_t)src * (uint32_t)p.lda + (uint32_t)(akoff + per * Kb + c * 8)),
                  smem + per * SA + (j * SK_THR + wave * 64) * 8);
     }
+  auto load_weights = [&](auto nt) {
 #pragma unroll
-  for (int t = 0; t < NB; ++t)
+    for (int t = 0; t < NB; ++t)
 #pragma unroll
-    for (int j = 0; j < B_ROUNDS; ++j) {
-      const int Ps = j * SK_THR + tid;
-      const int row = Ps >> 3;
-      const int c = (Ps & 7) ^ swz2(row);
-      int n = n0g + t * BN + row;
-      n = n < u.ncol ? n : u.ncol - 1;
-      const u16* bp = (n < p.ncols[0] ? Bw0 + (int64_t)n * Kb : Bw1 + (int64_t)(n - p.ncols[0]) * Kb) + c * 8;
-      load_lds16_nt(bp, smem + PER * SA + t * SBt + (j * SK_THR + wave * 64) * 8);
-    }
+      for (int j = 0; j < B_ROUNDS; ++j) {
+        const int Ps = j * SK_THR + tid;
+        const int row = Ps >> 3;
+        const int c = (Ps & 7) ^ swz2(row);
+        int n = n0g + t * BN + row;
+        n = n < u.ncol ? n : u.ncol - 1;
+        const u16* bp = (n < p.ncols[0] ? Bw0 + (int64_t)n * Kb : Bw1 + (int64_t)(n - p.ncols[0]) * Kb) + c * 8;
+        load_lds16_w<decltype(nt)::value>(bp, smem + PER * SA + t * SBt + (j * SK_THR + wave * 64) * 8);
+      }
+  };
+  if (u.shared)
+    load_weights(std::false_type{});
+  else
+    load_weights(std::true_type{});
   wait_vmcnt<0>();
   bar();
   f32x16 acc[NB];
@@ -1575,10 +1601,10 @@ __device__ __forceinline__ void skinny_wide_body(const SkinnyBatch& b, u16* smem
   }
 }
 
-template <int NB, int PER>
+template <int NB, int PER, WeightUse W>
 __global__ __launch_bounds__(SK_THR) void k_gemm_skinny_wide(SkinnyBatch b) {
   __shared__ __attribute__((aligned(1024))) u16 smem[skinny_wide_lds(NB, PER)];
-  skinny_wide_body<NB, PER>(b, smem);
+  skinny_wide_body<NB, PER, W>(b, smem);
 }
 
 // Hi/lo products of one weight slab (wide) and of two in one launch: a tree's
@@ -1586,15 +1612,16 @@ __global__ __launch_bounds__(SK_THR) void k_gemm_skinny_wide(SkinnyBatch b) {
 // few loads, so the one-slab products' workgroups take four column tiles (40 KB
 // and 4 bytes: three workgroups per compute unit). Tree T = 16, gate|up 21 -> 19
 // us, down 36 -> 31 us.
+template <WeightUse W>
 __global__ __launch_bounds__(SK_THR) void k_gemm_skinny_mix(SkinnyBatch b) {
   constexpr int ring = skinny_lds(2, 2), row = skinny_wide_lds(4, 2), lds = ring > row ? ring : row;
   __shared__ __attribute__((aligned(1024))) u16 smem[lds];
   int pi = 0;
   while (pi + 1 < b.n && (int)blockIdx.x >= b.base[pi + 1]) ++pi;
   if ((b.wide_mask >> pi) & 1)
-    skinny_wide_body<4, 2, true>(b, smem);
+    skinny_wide_body<4, 2, W, true>(b, smem);
   else
-    skinny_body<2, 2>(b, smem);
+    skinny_body<2, 2, W>(b, smem);
 }
 
 template <int BM, int BN>
@@ -1935,11 +1962,9 @@ hipError_t launch_gemm_lo8(const GemmArgs& g, int ofmt, int grid_tiles, hipStrea
   return hipGetLastError();
 }
 
-hipError_t launch_gemm_skinny_batch(const GemmArgs* g, const int* ofmt, const int* grid_tiles, int n,
+template <WeightUse W>
+static hipError_t launch_skinny(const GemmArgs* g, const int* ofmt, const int* grid_tiles, int n,
                                     hipStream_t s) {
-  if (n < 1 || n > kSkinnyMaxProblems) return hipErrorInvalidValue;
-  for (int i = 0; i < n; ++i)
-    if (!x16_shape_ok(g[i], ofmt[i])) return hipErrorInvalidValue;
   SkinnyBatch b{};
   int wg = 0;
   for (int i = 0; i < n; ++i) {
@@ -1987,21 +2012,17 @@ hipError_t launch_gemm_skinny_batch(const GemmArgs* g, const int* ofmt, const in
     }
     bw.base[n] = wgw;
     if (wgw <= 0) return hipSuccess;
-    if (g[0].K == 2 * BK2)
-      hipLaunchKernelGGL((k_gemm_skinny_wide<4, 2>), dim3(wgw), dim3(SK_THR), 0, s, bw);
-    else
-      hipLaunchKernelGGL((k_gemm_skinny_wide<4, 1>), dim3(wgw), dim3(SK_THR), 0, s, bw);
+    if (g[0].K == 2 * BK2) {
+      if constexpr (W != W_ROUTER)
+        hipLaunchKernelGGL((k_gemm_skinny_wide<4, 2, W>), dim3(wgw), dim3(SK_THR), 0, s, bw);
+    } else {
+      hipLaunchKernelGGL((k_gemm_skinny_wide<4, 1, W>), dim3(wgw), dim3(SK_THR), 0, s, bw);
+    }
     return hipGetLastError();
   }
-  if (!g[0].tiles) {  // the router: a launch of its own
-    if (n != 1 || pair) return hipErrorInvalidValue;
-    if (max_steps <= 2)
-      hipLaunchKernelGGL((k_gemm_skinny<2, 1, true>), dim3(wg), dim3(SK_THR), 0, s, b);
-    else
-      hipLaunchKernelGGL((k_gemm_skinny<4, 1, true>), dim3(wg), dim3(SK_THR), 0, s, b);
-  } else if (pair && max_steps > 4) {
-    hipLaunchKernelGGL((k_gemm_skinny<3, 2>), dim3(wg), dim3(SK_THR), 0, s, b);
-  } else if (pair && max_steps > 2) {
+  if (W != W_ROUTER && pair && max_steps > 4) {
+    if constexpr (W != W_ROUTER) hipLaunchKernelGGL((k_gemm_skinny<3, 2, W>), dim3(wg), dim3(SK_THR), 0, s, b);
+  } else if (W != W_ROUTER && pair && max_steps > 2) {
     // at most two weight slabs: all of them in flight at once in 32 KB (and 4
     // bytes), four workgroups per compute unit instead of the 4-stage ring's
     // three, and one fetch of a slab for both halves. Tree T = 16 (ranks 128 and
@@ -2018,16 +2039,32 @@ hipError_t launch_gemm_skinny_batch(const GemmArgs* g, const int* ofmt, const in
                : skinny_grid(g[i], (int64_t)grid_tiles[i] * b.ntn[i]);
     }
     bm.base[n] = wgm;
-    if (bm.wide_mask)
-      hipLaunchKernelGGL(k_gemm_skinny_mix, dim3(wgm), dim3(SK_THR), 0, s, bm);
-    else
-      hipLaunchKernelGGL((k_gemm_skinny<2, 2>), dim3(wg), dim3(SK_THR), 0, s, b);
+    if constexpr (W != W_ROUTER) {
+      if (bm.wide_mask)
+        hipLaunchKernelGGL(k_gemm_skinny_mix<W>, dim3(wgm), dim3(SK_THR), 0, s, bm);
+      else
+        hipLaunchKernelGGL((k_gemm_skinny<2, 2, W>), dim3(wg), dim3(SK_THR), 0, s, b);
+    }
   } else if (max_steps <= 2) {
-    hipLaunchKernelGGL((k_gemm_skinny<2, 1>), dim3(wg), dim3(SK_THR), 0, s, b);
+    hipLaunchKernelGGL((k_gemm_skinny<2, 1, W>), dim3(wg), dim3(SK_THR), 0, s, b);
   } else {
-    hipLaunchKernelGGL((k_gemm_skinny<4, 1>), dim3(wg), dim3(SK_THR), 0, s, b);
+    hipLaunchKernelGGL((k_gemm_skinny<4, 1, W>), dim3(wg), dim3(SK_THR), 0, s, b);
   }
   return hipGetLastError();
+}
+
+hipError_t launch_gemm_skinny_batch(const GemmArgs* g, const int* ofmt, const int* grid_tiles, int n,
+                                    hipStream_t s) {
+  if (n < 1 || n > kSkinnyMaxProblems) return hipErrorInvalidValue;
+  bool once = true;
+  for (int i = 0; i < n; ++i) {
+    if (!x16_shape_ok(g[i], ofmt[i])) return hipErrorInvalidValue;
+    // the router (implicit dense tiles): a launch of its own
+    if (!g[i].tiles && (n != 1 || g[i].K != (g[i].Kb > 0 ? g[i].Kb : g[i].K))) return hipErrorInvalidValue;
+    once = once && g[i].node_rows_max > 0 && g[i].node_rows_max <= kSkinnyBM;
+  }
+  if (!g[0].tiles) return launch_skinny<W_ROUTER>(g, ofmt, grid_tiles, n, s);
+  return once ? launch_skinny<W_ONCE>(g, ofmt, grid_tiles, n, s) : launch_skinny<W_NODE>(g, ofmt, grid_tiles, n, s);
 }
 
 int skinny_grid(const GemmArgs& g, int64_t items_max) {

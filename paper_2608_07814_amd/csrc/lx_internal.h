@@ -284,6 +284,9 @@ struct GemmArgs {
   // tiles == null: implicit tiles of kSkinnyBM consecutive rows over
   // dense_rows rows of A (identity row map, weight index 0)
   int32_t dense_rows;
+  // skinny kernel: the most rows that a node can have (the batch's tokens); 0:
+  // not known
+  int32_t node_rows_max;
   // large-tile kernel: when widx_anc is set, a tile's weight index is
   // widx_fac[widx_anc[tile node]] (the factor of the tile node's ancestor at
   // another level; below 0: the tile is skipped) instead of its own

@@ -193,6 +193,21 @@ def test_tree_decode_on_the_two_slab_kernels(over, T):
     assert e <= TOL_BF16 and e <= TOL_DESIGN
 
 
+@pytest.mark.parametrize("T", [31, 32, 33, 47, 64])
+@pytest.mark.parametrize("over", [{"E": 8, "C": 2, "k": 8, "r": 64}, {"E": 8, "C": 2, "k": 8, "r": 128, "d": 512},
+                                  {"E": 64, "C": 16, "k": 8, "r": 64}])
+def test_skinny_row_tiles_of_a_node(over, T):
+    """Every expert on every token (and 8 of 64): nodes of one ragged row tile, one
+    full one, a full one and one row, two full ones: their weight loads differ."""
+    require_gpu()
+    p = make_problem(dict(config(1, d=320, f=192), **over), seed=T, T=T)
+    dl = lx.to_device(p.layer)
+    got = gpu_forward(p, dev_layer=dl)
+    e = err_ratio(got, _oracle(p))
+    say(f"skinny row tiles {over} T={T}: err/RMS = {e:.3e}")
+    assert e <= TOL_BF16 and e <= TOL_DESIGN
+
+
 def test_cfg4_tree_mixed_kernels():
     """T=100: the root level runs on the large-tile kernel while the sub and
     leaf levels (few rows per node) run on the skinny kernel."""

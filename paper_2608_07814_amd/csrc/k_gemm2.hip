@@ -78,8 +78,8 @@ __device__ __forceinline__ void load_lds16(const void* gptr, const void* lds_dst
 }
 
 // The same load with the non-temporal hint, for weights that a launch reads
-// once or from a few neighbouring workgroups (the skinny kernels and the 128-row
-// tiles): the stream then leaves the caches to what is read again (activations,
+// once (the skinny kernels, where one row tile reads them) or from a few
+// neighbouring workgroups (the 128-row tiles): the stream then leaves the caches to what is read again (activations,
 // intermediates, row lists). Without and with the hint: tree T = 777 leaf-level
 // input product 82 -> 66 us; tree T = 16 forward 184 -> 172 us, of it bucketing
 // 13 -> 11 and SwiGLU 16.5 -> 12.4; one token on the 4096 x 14336 layer 109 -> 103.

@@ -45,10 +45,12 @@ __device__ __forceinline__ bool first_valid(const int32_t* row, int j, int E) {
   return true;
 }
 
-// One thread per token, integer atomics on global memory (any E).
+// One thread per token, integer atomics on global memory (any E). (Token indexes
+// here and below are unsigned: with N near 2^31 a grid stride past the last token
+// leaves the signed range.)
 __global__ __launch_bounds__(256) void k_coact(const int32_t* __restrict__ ids, int N, int k, int E,
                                                uint32_t* __restrict__ fire, uint32_t* __restrict__ pair) {
-  for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < N; t += gridDim.x * blockDim.x) {
+  for (uint32_t t = blockIdx.x * blockDim.x + threadIdx.x; t < (uint32_t)N; t += gridDim.x * blockDim.x) {
     const int32_t* row = ids + (int64_t)t * k;
     for (int a = 0; a < k; ++a) {
       if (!first_valid(row, a, E)) continue;
@@ -92,11 +94,11 @@ __global__ __launch_bounds__(kCoactThr) void k_coact_bits(const int32_t* __restr
   const bool own = bi < 32 && bi + 32 * (int)blockIdx.y < E && bj < E;
   const int ei = bi + 32 * blockIdx.y;
   uint32_t cnt[4] = {};
-  for (int t0 = blockIdx.x * kCoactTok; t0 < N; t0 += gridDim.x * kCoactTok) {
+  for (uint32_t t0 = blockIdx.x * kCoactTok; t0 < (uint32_t)N; t0 += gridDim.x * kCoactTok) {
     for (int i = tid; i < 128 * kCoactPitch; i += kCoactThr) s_mask[i] = 0u;
     __syncthreads();
-    const int t = t0 + tid;
-    if (t < N) {
+    const uint32_t t = t0 + tid;
+    if (t < (uint32_t)N) {
       const int32_t* row = ids + (int64_t)t * k;
       for (int a0 = 0; a0 < k; a0 += 8) {
         int e[8];
@@ -412,7 +414,7 @@ hipError_t launch_coact(const int32_t* ids, int N, int k, int E, uint32_t* fire,
                                               (unsigned)std::min(4, (E + 31) / 32)),
                          dim3(kCoactThr), 0, s, ids, N, k, E, fire, pair);
     else
-      hipLaunchKernelGGL(k_coact, dim3((unsigned)std::min((N + 255) / 256, 512)), dim3(256), 0, s, ids, N, k, E, fire,
+      hipLaunchKernelGGL(k_coact, dim3((unsigned)std::min<int64_t>(((int64_t)N + 255) / 256, 512)), dim3(256), 0, s, ids, N, k, E, fire,
                          pair);
   }
   hipLaunchKernelGGL(k_npmi, ge, dim3(256), 0, s, fire, pair, N, E, dist);

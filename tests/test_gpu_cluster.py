@@ -78,6 +78,28 @@ def test_counts_and_kmedoids_at_the_mask_edges(E, C, prot):
         assert np.array_equal(cl, c0) and np.array_equal(fo, o0) and np.array_equal(dom, d0) and it[0] == it0
 
 
+@pytest.mark.parametrize("E", [4, 200])
+def test_counts_of_the_most_tokens(E):
+    """2^31 - 1 tokens, one expert each (8.6 GB of ids): the grid strides stay in
+    range up to the last token, on the masks and on the per-token atomics."""
+    require_gpu()
+    N = 2 ** 31 - 1
+    say(f"cluster counts of {N} tokens, E={E}")
+    ids = torch.empty(N, 1, dtype=torch.int32, device="cuda")
+    step = 1 << 28
+    for a in range(0, N, step):
+        n = min(step, N - a)
+        ids[a:a + n, 0] = (torch.arange(n, device="cuda") + a) % E
+    fire, pair, dist = lx.coact_distance(ids, E)
+    torch.cuda.synchronize()
+    want = np.full(E, N // E, np.int64)
+    want[:N % E] += 1
+    assert np.array_equal(fire.cpu().numpy().astype(np.int64), want)
+    assert int(pair.abs().max()) == 0 and float(dist.max()) == 2.0
+    del ids
+    torch.cuda.empty_cache()
+
+
 def test_kmedoids_metric_large_and_max_iter():
     """E = 1024 points of a Euclidean metric (ties improbable), then the
     iteration cap: max_iter = 0 keeps the seeds' assignment, 1 one update."""

@@ -1,6 +1,6 @@
 """Set-up that is due once per device: every device gets its own, a failure is
 reported and tried again, and what is done is not repeated."""
-from host_rules import run_driver
+from host_rules import run_program
 
 BODY = """
     static lx::DeviceOnce once;
@@ -18,7 +18,7 @@ def test_device_once(tmp_path):
         ((1, 0), (0, 3)), ((1, 7), (0, 3)), ((63, 7), (7, 4)), ((63, 0), (0, 5)), ((63, 7), (0, 5)),
         ((64, 0), (0, 6)), ((64, 7), (7, 7)), ((-1, 0), (0, 8)), ((0, 7), (0, 8)),
     ]
-    rows = run_driver(tmp_path, "lx_device_once.h", BODY, [s for s, _ in steps])
+    rows = run_program(tmp_path, "lx_device_once.h", BODY, [s for s, _ in steps])
     assert [tuple(map(int, r)) for r in rows] == [want for _, want in steps]
 
 

@@ -3,7 +3,7 @@ library asks for, and the rotation log (stored and loaded 16 bytes at a time) on
 a 16-byte boundary."""
 import random
 
-from host_rules import run_driver
+from host_rules import run_program
 from paper_2608_07814_amd import lorex as lx
 
 BODY = """
@@ -26,7 +26,7 @@ def test_layout(tmp_path):
         cases.append((rows, cols, rng.choice((-1, l, l + rng.randint(0, 400))), l))
     L = lx.lib()
     odd = 0
-    for (rows, cols, np_, l), row in zip(cases, run_driver(tmp_path, "lx_stage3_ws.h", BODY, cases)):
+    for (rows, cols, np_, l), row in zip(cases, run_program(tmp_path, "lx_stage3_ws.h", BODY, cases)):
         *at, part, total, parts = map(int, row)
         lp, w = l + (l & 1), np_ >= 0
         n = max(np_, 0)

@@ -5,7 +5,7 @@ import random
 
 import pytest
 
-from host_rules import run_driver
+from host_rules import run_program
 
 BODY = """
     int N, work, T, k, ncol, K, part, bn0;
@@ -17,7 +17,7 @@ SHAPES = {(256, 256), (256, 128), (256, 64), (128, 128), (128, 64)}
 
 
 def _pick(tmp_path, cases):
-    return [(int(a), int(b), int(c), float(d), float(e)) for a, b, c, d, e in run_driver(tmp_path, "lx_tiles.h", BODY, cases)]
+    return [(int(a), int(b), int(c), float(d), float(e)) for a, b, c, d, e in run_program(tmp_path, "lx_tiles.h", BODY, cases)]
 
 
 def _products(E, C, d, f, r):
